@@ -163,10 +163,14 @@ typedef struct {
  *              iterations, x in LDS; n <= 32768, quadratic or entropy g),
  *              PDBO_CSR_ROWS (one launch per iteration over all rows, the
  *              restarts of a row in adjacent lanes; any n, any g), or
- *              PDBO_CSR_AUTO (resident when it fits and B >= 128).  With
+ *              PDBO_CSR_AUTO (resident when it fits and B >= 128, or with fewer
+ *              restarts when its iteration is estimated shorter than two
+ *              launches; the run is then bit for bit that of the row-parallel
+ *              path, its trace included, and graph_chunk has nothing to do).  With
  *              n <= 8192 the resident kernel stages its packed entries
  *              interleaved by slices of 64 rows when that takes no more LDS
- *              than CSR order (same sums in the same order, so the same
+ *              than CSR order, and instances with weights up to 2048 stage
+ *              them by position (same sums in the same order, so the same
  *              results); PDBO_CSR_SLICED=0 keeps CSR order.
  *   graph_chunk  dense and row-parallel CSR paths: 0 = eager launches;
  *              K > 0 (even) = capture K iterations in one hipGraph and replay it.

@@ -39,6 +39,7 @@ UNITS = [
     ("dense.hip", "dense_p2.o", ["-DPDBO_DENSE_PART=2"]),
     ("dense.hip", "dense_p3.o", ["-DPDBO_DENSE_PART=3"]),
     ("sparse.hip", "sparse.o", []),
+    ("resident.hip", "resident.o", []),
     ("maxsat.hip", "maxsat.o", []),
     ("spmm.hip", "spmm.o", []),
     ("cert.hip", "cert.o", []),

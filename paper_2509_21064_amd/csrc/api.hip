@@ -34,6 +34,18 @@ constexpr int kMaxLimbs = 4;  // int8 limbs of the dense exact evaluation
 // the automatic CSR choice gives each restart a workgroup of its own only when
 // there are enough restarts to occupy the chip
 constexpr int kResidentMinB = 128;
+// and, with fewer, when an iteration of the resident kernel is estimated
+// shorter than the row-parallel path's two launches.  Measured (us an
+// iteration, resident against row-parallel, B = 10): n = 1000, degree 3:
+// 0.7 / 11.1; n = 8000, degree 12: 8.4 / 12.4; n = 16000, degree 3: 8.7 / 12.6,
+// degree 12: 17.8 / 13.8; degree 100: n = 2000 7.8 / 16.2, n = 4000 15.4 / 16.5,
+// n = 16000 144 / 24.  B = 100: n = 2000, degree 6: 1.5 / 26; n = 16000,
+// degree 12: 18 / 49.
+double resident_us(int n, int64_t words) {
+  const double per_word = n > 8192 ? 9e-5 : n > 4096 ? 7e-5 : 4e-5;
+  return 0.4 + 2.5e-4 * n + per_word * (double)words;
+}
+double rowpar_us(int B) { return 9.0 + 0.1 * B; }
 constexpr int64_t kI64Max = LLONG_MAX;
 
 int roundup(int v, int a) { return (v + a - 1) / a * a; }
@@ -1567,6 +1579,87 @@ static pdbo_status persistent_supported(const pdbo_params* p) {
 static pdbo_status spmm_init(const CsrCanon* C, const RealCanon* R, const pdbo_params* p,
                              void* stream, pdbo_ctx** out);
 
+// The layout of the resident kernel (CsrDev::rent): entries of the rows
+// order[q] by slices of 64 positions q; a row's full groups of four entries,
+// then one group with what is left of it (one to three), each row's entries in
+// order.  Padding entries have weight 0.
+struct ResLayout {
+  std::vector<uint32_t> ent;
+  std::vector<int2> slice;
+  std::vector<int32_t> cp;
+};
+
+static int64_t res_layout_words(const CsrCanon& C, const std::vector<int32_t>& order,
+                                std::vector<int2>* slice) {
+  const int n = C.n;
+  int64_t tot = 0;
+  for (int s = 0; s < (n + 63) / 64; ++s) {
+    int nf = 0, rest = 0;
+    for (int q = s * 64; q < std::min(n, s * 64 + 64); ++q) {
+      const int len = C.rp[order[q] + 1] - C.rp[order[q]];
+      nf = std::max(nf, len / 4);
+      rest |= len % 4 != 0;
+    }
+    if (slice) slice->push_back(make_int2((int)tot, nf << 1 | rest));
+    tot += 256 * (int64_t)(nf + rest);
+  }
+  return tot;
+}
+
+static void res_layout(const CsrCanon& C, const std::vector<int32_t>& order, ResLayout& L) {
+  const int n = C.n, np = csr_resident_rows(n) * 1024, nc = csr_resident_copies(n);
+  const int64_t tot = res_layout_words(C, order, &L.slice);
+  L.ent.assign((size_t)std::max<int64_t>(tot, 4), 0u);
+  L.cp.assign(np, 0);
+  std::vector<int32_t> pos(n);
+  std::vector<uint16_t> off((size_t)nc * n);  // byte offsets by position and copy
+  for (int q = 0; q < n; ++q) {
+    pos[order[q]] = q;
+    L.cp[q] = (int32_t)C.cp[order[q]];
+    for (int c = 0; c < nc; ++c) off[(size_t)q * nc + c] = (uint16_t)(4 * csr_resident_word(n, c, q));
+  }
+  for (size_t s = 0; s < L.slice.size(); ++s) {
+    const int nf = L.slice[s].y >> 1, ng = nf + (L.slice[s].y & 1);
+    for (int k = 0; k < 4 * ng; ++k) {  // the wave's gather k: entry k % 4 of group k / 4
+      uint32_t* to = &L.ent[(size_t)L.slice[s].x + 256 * (size_t)(k / 4) + k % 4];
+      for (int half = 0; half < 2; ++half) {
+        // A gather takes as many cycles as the fullest of the 32 banks has
+        // addresses, for each half of the wave: every lane takes the copy whose
+        // bank is the emptiest so far.  Lanes without an entry repeat an
+        // address of the half (a broadcast, no cycle of its own).
+        int load[32] = {};
+        int some = -1;
+        int32_t pick[32];
+        for (int l = 0; l < 32; ++l) {
+          pick[l] = -1;
+          const int q = (int)s * 64 + half * 32 + l;
+          if (q >= n) continue;
+          const int b = C.rp[order[q]], len = C.rp[order[q] + 1] - b;
+          // left-over entries are in the slice's last group whatever the row's own full groups
+          const int e = k < 4 * nf ? (k < len / 4 * 4 ? k : -1)
+                                   : (k - 4 * nf < len % 4 ? len / 4 * 4 + k - 4 * nf : -1);
+          if (e < 0) continue;
+          const uint16_t* o = &off[(size_t)pos[C.col[b + e]] * nc];
+          int best = 0;
+          for (int c = 1; c < nc; ++c)
+            if (load[o[c] / 4 % 32] < load[o[best] / 4 % 32]) best = c;
+          ++load[o[best] / 4 % 32];
+          const _Float16 w = (_Float16)(float)C.val[b + e];
+          uint16_t wb;
+          std::memcpy(&wb, &w, 2);
+          to[4 * (half * 32 + l)] = (uint32_t)o[best] | ((uint32_t)wb << 16);
+          pick[l] = o[best];
+          some = o[best];
+        }
+        if (some < 0) continue;
+        for (int l = 0; l < 32; ++l)
+          if (pick[l] < 0) to[4 * (half * 32 + l)] = (uint32_t)some;
+      }
+    }
+  }
+  L.slice.resize(np / 64, make_int2(0, 0));
+}
+
 static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stream, pdbo_ctx** out) {
   if (p->eval_every != 1) return fail(nullptr, PDBO_EUNSUPPORTED, "the CSR path evaluates every iteration");
   if (p->tile > PDBO_CSR_ROWS)
@@ -1578,8 +1671,36 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
   const bool compact = n <= 65536 && C.amax <= 32767;  // packed 16-bit column / 16-bit value
   const bool fits = csr_fits(n, (int64_t)C.col.size(), compact, nullptr);
   int path = p->tile;
-  if (path == PDBO_CSR_AUTO)
-    path = (fits && p->B >= kResidentMinB && persistent_ok(p)) ? PDBO_CSR_RESIDENT : PDBO_CSR_ROWS;
+  int64_t cmax = 0;
+  for (int i = 0; i < n; ++i) cmax = std::max<int64_t>(cmax, C.cp[i] < 0 ? -C.cp[i] : C.cp[i]);
+  // a wave of the 1024-thread kernels sums at most 64 x 8 rows
+  const int64_t lim32 = int64_t(1) << 31;
+  const bool small32 = 512 * C.rowabs < lim32 && 512 * cmax < lim32;
+  const bool tot32 = small32 && (int64_t)n * C.rowabs < lim32 && (int64_t)n * cmax < lim32;
+  // rows by decreasing degree (ties by index): a wave's rows then have nearly
+  // the same number of entries
+  std::vector<int32_t> order(n);
+  for (int i = 0; i < n; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+    return C.rp[a + 1] - C.rp[a] > C.rp[b + 1] - C.rp[b];
+  });
+  // resident.hip: weights exact in float16, twice a row's sum exact in float32,
+  // totals in int32, positions within a 16-bit byte offset
+  const bool res_ok = C.amax <= 2048 && C.rowabs < (1 << 23) && tot32 && csr_resident_rows(n) > 0 &&
+                      n <= 16384 && persistent_ok(p);
+  const bool few = path == PDBO_CSR_AUTO && p->B < kResidentMinB;
+  const int64_t res_words = res_ok ? res_layout_words(C, order, nullptr) : 0;
+  bool seq = false;
+  if (path == PDBO_CSR_AUTO) {
+    if (fits && p->B >= kResidentMinB && persistent_ok(p)) {
+      path = PDBO_CSR_RESIDENT;
+    } else if (res_ok && few && resident_us(n, res_words) < rowpar_us(p->B)) {
+      path = PDBO_CSR_RESIDENT;
+      seq = true;
+    } else {
+      path = PDBO_CSR_ROWS;
+    }
+  }
   if (path == PDBO_CSR_ROWS) return spmm_init(&C, nullptr, p, stream, out);
   STCHK(persistent_supported(p));
   if (!fits)
@@ -1601,25 +1722,12 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
     d.nnz = nnz;
     d.kos = (float)((double)C.kappa / p->scale);
     d.gp = make_gp(p);
-    int64_t cmax = 0;
-    for (int i = 0; i < n; ++i) cmax = std::max<int64_t>(cmax, C.cp[i] < 0 ? -C.cp[i] : C.cp[i]);
-    {
-      // a wave of the 1024-thread kernel sums at most 64 x 8 rows
-      const int64_t lim = int64_t(1) << 31;
-      d.small32 = (512 * C.rowabs < lim && 512 * cmax < lim) ? 1 : 0;
-      d.tot32 = (d.small32 && (int64_t)n * C.rowabs < lim && (int64_t)n * cmax < lim) ? 1 : 0;
-    }
+    d.small32 = small32 ? 1 : 0;
+    d.tot32 = tot32 ? 1 : 0;
     int32_t* rp = nullptr;
     STCHK(dalloc(c, &rp, n + 1));
     HIPCHK(c, hipMemcpyAsync(rp, C.rp.data(), (n + 1) * 4, hipMemcpyHostToDevice, c->stream));
     d.row_ptr = rp;
-    // rows by decreasing degree (ties by index): a wave's rows then have
-    // nearly the same number of entries
-    std::vector<int32_t> order(n);
-    for (int i = 0; i < n; ++i) order[i] = i;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-      return C.rp[a + 1] - C.rp[a] > C.rp[b + 1] - C.rp[b];
-    });
     int32_t* ord = nullptr;
     STCHK(dalloc(c, &ord, n));
     HIPCHK(c, hipMemcpyAsync(ord, order.data(), (size_t)n * 4, hipMemcpyHostToDevice, c->stream));
@@ -1627,6 +1735,7 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
     // host staging lives until the stream is synchronised at the end of init
     std::vector<uint32_t> pk, psl;
     std::vector<int32_t> slo;
+    ResLayout rl;
     int32_t* col = nullptr;
     int32_t* val = nullptr;
     STCHK(dalloc(c, &col, nnz));
@@ -1645,6 +1754,12 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
       d.packed = dp;
     }
     const char* sl_env = std::getenv("PDBO_CSR_SLICED");
+    // The resident kernel runs the same sums as csr_persistent.  It takes the
+    // instances the automatic choice sends here, and of those sent here by the
+    // caller the ones with room for two copies of x and int32 totals, whose
+    // variant's name then still tells the size class.
+    const bool two_sums = !seq && res_ok && !(sl_env && std::atoi(sl_env) == 0) &&
+                          (p->tile == PDBO_CSR_AUTO || (n <= 8192 && csr_double_buffered(n, nnz, compact)));
     if (compact && n <= 8192 && !(sl_env && std::atoi(sl_env) == 0)) {
       // the interleaved layout of the 1024-thread kernels (slices of 64
       // positions, each as long as its longest row), used when it takes no
@@ -1660,7 +1775,9 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
         tot += (int64_t)64 * lmax;
       }
       auto a16 = [](int64_t v) { return (v + 15) / 16 * 16; };
-      if (a16(4 * tot) <= a16(4 * (int64_t)(n + 1)) + a16(4 * nnz)) {
+      const bool sliced = a16(4 * tot) <= a16(4 * (int64_t)(n + 1)) + a16(4 * nnz);
+      d.sliced = sliced ? 1 : 0;
+      if (sliced && !seq && !two_sums) {
         psl.assign((size_t)tot, 0u);
         for (int q = 0; q < n; ++q) {
           const int i = order[q];
@@ -1677,6 +1794,23 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
         d.slice = dso;
         d.nsl = tot;
       }
+    }
+    if (seq || two_sums) {
+      res_layout(C, order, rl);
+      uint32_t* re = nullptr;
+      int2* rs = nullptr;
+      int32_t* rc = nullptr;
+      STCHK(dalloc(c, &re, rl.ent.size()));
+      STCHK(dalloc(c, &rs, rl.slice.size()));
+      STCHK(dalloc(c, &rc, rl.cp.size()));
+      HIPCHK(c, hipMemcpyAsync(re, rl.ent.data(), rl.ent.size() * 4, hipMemcpyHostToDevice, c->stream));
+      HIPCHK(c, hipMemcpyAsync(rs, rl.slice.data(), rl.slice.size() * sizeof(int2), hipMemcpyHostToDevice,
+                               c->stream));
+      HIPCHK(c, hipMemcpyAsync(rc, rl.cp.data(), rl.cp.size() * 4, hipMemcpyHostToDevice, c->stream));
+      d.rent = re;
+      d.nrent = res_words;
+      d.rslice = rs;
+      d.rcp = rc;
     }
     std::vector<float> hcps(ld, 0.f);
     std::vector<int64_t> hcp(ld, 0);
@@ -1701,6 +1835,17 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
     STCHK(dalloc(c, &d.Flast, B));
     STCHK(dalloc(c, &c->inc_d, 1));
     STCHK(dalloc(c, &c->best_x_d, n));
+    if (seq) {
+      d.seq = 1;
+      d.trace_cap = kTraceCap;
+      STCHK(dalloc(c, &d.rtr, (size_t)B * kResTrace));
+      STCHK(dalloc(c, &d.rtl, B));
+      STCHK(dalloc(c, &d.trace, kTraceCap));
+      STCHK(dalloc(c, &d.trace_len, 1));
+      STCHK(dalloc(c, &d.t_dev, 1));
+      d.inc = c->inc_d;
+      d.best_x = c->best_x_d;
+    }
     HIPCHK(c, launch_fill_i64(d.rbestF, kI64Max, B, c->stream));
     HIPCHK(c, launch_fill_i64(d.rbestT, kI64Max, B, c->stream));
     Incumbent init{kI64Max, -1, -1, 0};
@@ -2168,6 +2313,7 @@ pdbo_status qubo_gda_result(pdbo_ctx* c, pdbo_result* r) {
   const int n = c->n_of[0];
   if (c->kind == 3) return fill_result(c, c->spmm.inc, c->spmm.best_x, n, r);
   if (c->kind == 4) return fill_result(c, c->kcut.inc, c->kcut.best_x, n, r);
+  if (c->kind == 1 && c->csr.seq) return fill_result(c, c->inc_d, c->best_x_d, n, r);
   if (c->kind == 1)
     HIPCHK(c, launch_restart_best(c->csr.rbestF, c->csr.rbestT, c->csr.rbestTs, c->csr.best_xr, B,
                                   n, c->inc_d, c->best_x_d, c->stream));
@@ -2348,6 +2494,8 @@ pdbo_status qubo_gda_set_state(pdbo_ctx* c, const float* x, const float* y, int6
                              c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
   }
+  if (c->kind == 1 && c->csr.seq)
+    HIPCHK(c, hipMemcpyAsync(c->csr.t_dev, &t, sizeof(t), hipMemcpyHostToDevice, c->stream));
   if (c->kind == 0) {
     HIPCHK(c, hipMemcpyAsync(c->insts_h[0].t_dev, &t, sizeof(t), hipMemcpyHostToDevice, c->stream));
     // the rounded iterate no longer follows the recorded changes
@@ -2437,6 +2585,10 @@ pdbo_status qubo_gda_restart(pdbo_ctx* c, const double* x0) {
     HIPCHK(c, launch_fill_i64(rbF, kI64Max, B, c->stream));
     HIPCHK(c, launch_fill_i64(rbT, kI64Max, B, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->inc_d, &init, sizeof(init), hipMemcpyHostToDevice, c->stream));
+    if (c->kind == 1 && c->csr.seq) {
+      HIPCHK(c, launch_fill_i64(c->csr.t_dev, 0, 1, c->stream));
+      HIPCHK(c, launch_fill_i32(c->csr.trace_len, 0, 1, c->stream));
+    }
   }
   // the time origin is the first step after the restart
   HIPCHK(c, launch_fill_i64((int64_t*)c->ts0_d, 0, 1, c->stream));
@@ -2763,6 +2915,8 @@ pdbo_status qubo_dual_bound(pdbo_ctx* c, double ybar, int32_t iters, double* low
                                 c->stream));
   } else if (c->kind == 1) {
     CsrDev d = c->csr;
+    d.rtr = nullptr;  // no incumbent here
+    d.t_dev = nullptr;
     d.B = 1;
     d.X = x0;
     d.Y = c->cert_y;
@@ -3227,6 +3381,9 @@ static pdbo_status trace_records(pdbo_ctx* c, int32_t cap, int64_t* t, int64_t* 
   } else if (c->kind == 4) {
     trace_d = c->kcut.trace;
     len_d = c->kcut.trace_len;
+  } else if (c->kind == 1 && c->csr.seq) {
+    trace_d = c->csr.trace;
+    len_d = c->csr.trace_len;
   } else {
     return PDBO_OK;
   }

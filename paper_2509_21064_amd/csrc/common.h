@@ -140,6 +140,20 @@ __device__ __forceinline__ void gda_update(float x, float y, float G, const GdaP
   yn = fmaf(p.beta, g_value(x, p.gkind, p.deg), y);
 }
 
+// gda_update for a wave none of whose lanes can be perturbed: y > 0 in all of
+// them (y starts at y0 > 0 and falls by beta |g| an iteration, so for hundreds
+// of iterations), which saves a third of the instructions.
+__device__ __forceinline__ void gda_update_wave(float x, float y, float G, const GdaP& p,
+                                                float& xn, float& yn) {
+  if (__builtin_amdgcn_ballot_w64(!(y > 0.f))) {
+    gda_update(x, y, G, p, xn, yn);
+  } else {
+    const float dL = fmaf(y, g_deriv(x, p.gkind, p.deg), G);
+    xn = fminf(fmaxf(fmaf(-p.alpha, dL, x), 0.f), 1.f);
+    yn = fmaf(p.beta, g_value(x, p.gkind, p.deg), y);
+  }
+}
+
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
   uint32_t u = __float_as_uint(f);
   u += 0x7fffu + ((u >> 16) & 1u);
@@ -286,16 +300,43 @@ struct CsrDev {
   const int32_t* slice;   // [ceil(n / 64)]
   int64_t nsl;            // words of psl
   int64_t nnz;
+  // resident.hip's layout (null: the instance runs on csr_persistent): entries
+  // in positions, {byte offset of a copy of x_j | float16 weight << 16}, by
+  // slices of 64 positions, each a number of full groups of four entries (16
+  // bytes per lane) and at most one group of the entries left over
+  const uint32_t* rent;
+  int64_t nrent;          // words of rent
+  const int2* rslice;     // per slice {first word, full groups << 1 | left-over group}, zero past the last
+  const int32_t* rcp;     // c' by position, zero past n
+  // contexts that stand in for the row-parallel path: its order of the sums,
+  // and its incumbent and trace, kept on the device (else null)
+  int seq;
+  int sliced;             // the interleaved layout takes no more LDS than CSR order (psl above)
+  int trace_cap;
+  TraceRec* rtr;          // [B][kResTrace] the restarts' own improvements in one launch
+  int32_t* rtl;           // [B] their number
+  Incumbent* inc;
+  uint8_t* best_x;
+  TraceRec* trace;
+  int32_t* trace_len;
+  int64_t* t_dev;
   int n, ld, B, kappa;
   int small32;            // 512 * max_i sum_j |Ahat_ij| and 512 * max_i |c'_i| are below 2^31
   int tot32;              // n times each of those is below 2^31 too: a restart's totals fit int32
   float kos;
   GdaP gp;
 };
+bool csr_double_buffered(int n, int64_t nnz, bool packed);
 bool csr_fits(int n, int64_t nnz, bool packed, size_t* lds_bytes);
 const char* csr_variant_name(const CsrDev& d, bool packed);
 hipError_t launch_csr_persistent(const CsrDev& d, bool packed, int64_t t0, int nsteps,
                                  hipStream_t s);
+// ---- launchers (resident.hip)
+constexpr int kResTrace = 1024;  // records per restart and launch
+int csr_resident_rows(int n);    // positions per thread, 0 when n is too large
+int csr_resident_copies(int n);  // copies of x in LDS
+int csr_resident_word(int n, int c, int p);  // word of position p in copy c
+hipError_t launch_csr_resident(const CsrDev& d, int64_t t0, int nsteps, hipStream_t s);
 hipError_t launch_csr_grad(const CsrDev& d, const float* X, float* G, int nb, hipStream_t s);
 hipError_t launch_csr_eval(const CsrDev& d, const int8_t* xr, int nb, int64_t* F, hipStream_t s);
 
