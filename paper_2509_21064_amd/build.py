@@ -41,6 +41,7 @@ UNITS = [
     ("sparse.hip", "sparse.o", []),
     ("resident.hip", "resident.o", []),
     ("maxsat.hip", "maxsat.o", []),
+    ("satres.hip", "satres.o", []),
     ("spmm.hip", "spmm.o", []),
     ("cert.hip", "cert.o", []),
     ("kcut.hip", "kcut.o", []),

@@ -3123,6 +3123,123 @@ pdbo_status kcut_gda_init(const pdbo_kcut* g, const pdbo_params* p, void* stream
   return PDBO_OK;
 }
 
+// satres.hip's layout of a formula (SatDev::pent): the occurrence lists of the
+// positions, in groups of four per lane (k planes of two words: the codes of
+// the other literals, the signed weights), each list in the order the kernels of
+// maxsat.hip sum it in: its owned clauses first for 3-SAT, else as it stands.
+struct SatLayout {
+  std::vector<uint32_t> ent;
+  std::vector<int2> slice;
+  std::vector<uint16_t> lit;
+};
+
+static bool sat_layout(int n, int m, int k, const std::vector<int32_t>& ptr,
+                       const std::vector<int32_t>& inc, const std::vector<int32_t>& codes,
+                       const std::vector<int32_t>& ord, const std::vector<int32_t>& pos, SatLayout& L) {
+  const int ns = (n + 63) / 64, nc = satres_copies(n, k), blk = 128 * k;
+  int64_t tot = 0;
+  for (int s = 0; s < ns; ++s) {
+    int nf = 0, rest = 0;
+    for (int q = s * 64; q < std::min(n, s * 64 + 64); ++q) {
+      const int len = ptr[ord[q] + 1] - ptr[ord[q]];
+      nf = std::max(nf, len / 4);
+      rest |= len % 4 != 0;
+    }
+    L.slice.push_back(make_int2((int)tot, nf << 1 | rest));
+    tot += (int64_t)blk * (nf + rest);
+    if (tot + blk > INT32_MAX) return false;
+  }
+  // one block more: the kernels read ahead by a group
+  L.ent.assign((size_t)(tot + blk), 0u);
+  // words of the literals by variable, sign (plain) and copy
+  std::vector<uint16_t> word((size_t)2 * n * nc);
+  for (int w = 0; w < 2 * n; ++w)
+    for (int c = 0; c < nc; ++c)
+      word[(size_t)w * nc + c] = (uint16_t)satres_word(n, c, 2 * pos[w >> 1] + (w & 1));
+  auto words_of = [&](int32_t code) {
+    return &word[(size_t)(2 * (code & 0x7fffffff) + (code < 0 ? 0 : 1)) * nc];
+  };
+  std::vector<int32_t> lists[64];  // the occurrences of a slice's positions in order
+  for (int s = 0; s < ns; ++s) {
+    const int nf = L.slice[s].y >> 1, ng = nf + (L.slice[s].y & 1);
+    for (int l = 0; l < 64; ++l) {
+      std::vector<int32_t>& li = lists[l];
+      li.clear();
+      const int q = s * 64 + l;
+      if (q >= n) continue;
+      const int b = ptr[ord[q]], e = ptr[ord[q] + 1];
+      auto owned = [&](int i) { return ((inc[(size_t)i * k + k - 1] >> 29) & 1) != 0; };
+      for (int i = b; i < e; ++i)
+        if (k != 3 || owned(i)) li.push_back(i);
+      if (k == 3)
+        for (int i = b; i < e; ++i)
+          if (!owned(i)) li.push_back(i);
+    }
+    for (int g = 0; g < ng; ++g)
+      for (int u = 0; u < 4; ++u)
+        for (int half = 0; half < 2; ++half) {
+          // A gather takes as many cycles as the fullest of the 32 banks has
+          // addresses, for each half of the wave.  Each factor comes from the
+          // copy whose bank is the emptiest so far; with one copy, the two
+          // first factors (whose order does not matter to their product) go to
+          // the two gathers the other way round when that is better.  Lanes
+          // without an occurrence repeat an address of the half.
+          uint16_t* to = (uint16_t*)&L.ent[(size_t)L.slice[s].x + (size_t)blk * g] + u;
+          int load[4][32] = {};
+          int some = -1;
+          bool none[32];
+          for (int l = 0; l < 32; ++l) {
+            const std::vector<int32_t>& li = lists[half * 32 + l];
+            const int len = (int)li.size(), full = len / 4;
+            const int r = g < nf ? (g < full ? 4 * g + u : -1) : (u < len % 4 ? 4 * full + u : -1);
+            none[l] = r < 0;
+            if (r < 0) continue;
+            const int32_t* E = &inc[(size_t)li[r] * k];
+            uint16_t* at = to + 4 * (half * 32 + l);
+            auto emptiest = [&](int o, const uint16_t* w) {
+              int best = 0;
+              for (int c = 1; c < nc; ++c)
+                if (load[o][w[c] % 32] < load[o][w[best] % 32]) best = c;
+              return w[best];
+            };
+            int o0 = 0;
+            if (nc == 1 && k > 2) {
+              const uint16_t a = *words_of(E[0]), b2 = *words_of(E[1]);
+              const int ab = std::max(load[0][a % 32], load[1][b2 % 32]);
+              const int ba = std::max(load[0][b2 % 32], load[1][a % 32]);
+              const bool swap = ba < ab || (ba == ab && load[0][b2 % 32] + load[1][a % 32] <
+                                                            load[0][a % 32] + load[1][b2 % 32]);
+              at[0] = swap ? b2 : a;
+              at[256] = swap ? a : b2;
+              ++load[0][at[0] % 32];
+              ++load[1][at[256] % 32];
+              o0 = 2;
+            }
+            for (int o = o0; o < k - 1; ++o) {
+              at[256 * o] = emptiest(o, words_of(E[o]));
+              ++load[o][at[256 * o] % 32];
+            }
+            some = l;
+            const float wt = (float)(E[k - 1] & 0xffffff);
+            const _Float16 h = (_Float16)((E[k - 1] >> 30) & 1 ? wt : -wt);
+            std::memcpy(&at[256 * (k - 1)], &h, 2);
+          }
+          if (some >= 0)
+            for (int l = 0; l < 32; ++l)
+              if (none[l])
+                for (int o = 0; o < k - 1; ++o)
+                  to[4 * (half * 32 + l) + 256 * o] = to[4 * (half * 32 + some) + 256 * o];
+        }
+  }
+  L.lit.resize((size_t)k * m);
+  for (int l = 0; l < k; ++l)
+    for (int j = 0; j < m; ++j) {
+      const int32_t code = codes[(size_t)j * k + l];
+      L.lit[(size_t)l * m + j] = (uint16_t)(2 * pos[code & 0x7fffffff] + (code < 0 ? 0 : 1));
+    }
+  return true;
+}
+
 pdbo_status maxsat_gda_init(const pdbo_maxsat* prob, const pdbo_params* p, void* stream,
                             pdbo_ctx** out) {
   if (!out) return fail(nullptr, PDBO_EINVAL, "out is NULL");
@@ -3179,7 +3296,8 @@ pdbo_status maxsat_gda_init(const pdbo_maxsat* prob, const pdbo_params* p, void*
 
   std::vector<uint64_t> pinc3;  // host staging, alive until init syncs
   std::vector<int32_t> slice;
-  std::vector<int32_t> ord, pptr, pinc;
+  SatLayout sl;
+  std::vector<int32_t> ord, posv, pptr, pinc;
   pdbo_ctx* c = new pdbo_ctx();
   c->kind = 2;
   c->n_of.push_back(n);
@@ -3195,53 +3313,83 @@ pdbo_status maxsat_gda_init(const pdbo_maxsat* prob, const pdbo_params* p, void*
     d.B = B;
     d.ios = (float)(1.0 / p->scale);
     d.gp = make_gp(p);
-    int32_t *dp = nullptr, *di = nullptr, *dl = nullptr, *dw = nullptr;
-    STCHK(dalloc(c, &dp, n + 1));
-    STCHK(dalloc(c, &di, inc.size()));
+    int32_t wmax = 0;
+    for (int j = 0; j < m; ++j) wmax = std::max(wmax, wv[j]);
+    // satres.hip takes the formula when its table fits in LDS and the weights
+    // are exact in float16 (PDBO_SAT_RESIDENT=0 keeps the general kernels)
+    const char* res_env = std::getenv("PDBO_SAT_RESIDENT");
+    const bool res = satres_copies(n, k) > 0 && wmax <= 2048 && !(res_env && std::atoi(res_env) == 0);
+    int32_t *dl = nullptr, *dw = nullptr;
     STCHK(dalloc(c, &dl, codes.size()));
     STCHK(dalloc(c, &dw, m));
-    HIPCHK(c, hipMemcpyAsync(dp, ptr.data(), (n + 1) * 4, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(di, inc.data(), inc.size() * 4, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(dl, codes.data(), codes.size() * 4, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(dw, wv.data(), m * 4, hipMemcpyHostToDevice, c->stream));
-    d.inc_ptr = dp;
-    d.inc = di;
     d.lits = dl;
     d.w = dw;
-    // position space of the persistent kernel: variables by decreasing
-    // occurrence count, their lists with the other literals' codes renamed
-    // to positions
+    // position space of the persistent kernels: variables by decreasing
+    // occurrence count
     ord.resize(n);
     for (int v = 0; v < n; ++v) ord[v] = v;
     std::stable_sort(ord.begin(), ord.end(), [&](int32_t a, int32_t b2) {
       return ptr[a + 1] - ptr[a] > ptr[b2 + 1] - ptr[b2];
     });
-    std::vector<int32_t> posv(n);
+    posv.resize(n);
     for (int q = 0; q < n; ++q) posv[ord[q]] = q;
     pptr.assign(n + 1, 0);
     for (int q = 0; q < n; ++q) pptr[q + 1] = pptr[q] + (ptr[ord[q] + 1] - ptr[ord[q]]);
-    pinc.resize(inc.size());
-    auto rename = [&](int32_t code) {
-      return (int32_t)(((uint32_t)code & 0x80000000u) | (uint32_t)posv[code & 0x7fffffff]);
-    };
-    for (int q = 0; q < n; ++q) {
-      const int v = ord[q];
-      for (int e = ptr[v], f = pptr[q]; e < ptr[v + 1]; ++e, ++f) {
-        for (int o = 0; o < k - 1; ++o) pinc[(size_t)f * k + o] = rename(inc[(size_t)e * k + o]);
-        pinc[(size_t)f * k + (k - 1)] = inc[(size_t)e * k + (k - 1)];
-      }
-    }
-    int32_t *dord = nullptr, *dpp = nullptr, *dpi = nullptr;
+    int32_t *dord = nullptr, *dpp = nullptr;
     STCHK(dalloc(c, &dord, n));
     STCHK(dalloc(c, &dpp, n + 1));
-    STCHK(dalloc(c, &dpi, pinc.size()));
     HIPCHK(c, hipMemcpyAsync(dord, ord.data(), (size_t)n * 4, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(dpp, pptr.data(), (size_t)(n + 1) * 4, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(dpi, pinc.data(), pinc.size() * 4, hipMemcpyHostToDevice, c->stream));
     d.order = dord;
     d.pinc_ptr = dpp;
-    d.pinc = dpi;
-    if (k == 3) {
+    if (!res) {
+      // variable-major lists, and by position with the other literals' codes
+      // renamed to positions
+      pinc.resize(inc.size());
+      auto rename = [&](int32_t code) {
+        return (int32_t)(((uint32_t)code & 0x80000000u) | (uint32_t)posv[code & 0x7fffffff]);
+      };
+      for (int q = 0; q < n; ++q) {
+        const int v = ord[q];
+        for (int e = ptr[v], f = pptr[q]; e < ptr[v + 1]; ++e, ++f) {
+          for (int o = 0; o < k - 1; ++o) pinc[(size_t)f * k + o] = rename(inc[(size_t)e * k + o]);
+          pinc[(size_t)f * k + (k - 1)] = inc[(size_t)e * k + (k - 1)];
+        }
+      }
+      int32_t *dp = nullptr, *di = nullptr, *dpi = nullptr;
+      STCHK(dalloc(c, &dp, n + 1));
+      STCHK(dalloc(c, &di, inc.size()));
+      STCHK(dalloc(c, &dpi, pinc.size()));
+      HIPCHK(c, hipMemcpyAsync(dp, ptr.data(), (n + 1) * 4, hipMemcpyHostToDevice, c->stream));
+      HIPCHK(c, hipMemcpyAsync(di, inc.data(), inc.size() * 4, hipMemcpyHostToDevice, c->stream));
+      HIPCHK(c, hipMemcpyAsync(dpi, pinc.data(), pinc.size() * 4, hipMemcpyHostToDevice, c->stream));
+      d.inc_ptr = dp;
+      d.inc = di;
+      d.pinc = dpi;
+    }
+    if (res) {
+      if (!sat_layout(n, m, k, ptr, inc, codes, ord, posv, sl))
+        return fail(c, PDBO_ERANGE, "MaxSAT occurrence slices exceed 2^31 words");
+      uint32_t* de = nullptr;
+      int2* ds = nullptr;
+      uint16_t* dli = nullptr;
+      int32_t* dpos = nullptr;
+      STCHK(dalloc(c, &de, sl.ent.size()));
+      STCHK(dalloc(c, &ds, sl.slice.size()));
+      STCHK(dalloc(c, &dli, sl.lit.size()));
+      STCHK(dalloc(c, &dpos, n));
+      HIPCHK(c, hipMemcpyAsync(de, sl.ent.data(), sl.ent.size() * 4, hipMemcpyHostToDevice, c->stream));
+      HIPCHK(c, hipMemcpyAsync(ds, sl.slice.data(), sl.slice.size() * sizeof(int2), hipMemcpyHostToDevice,
+                               c->stream));
+      HIPCHK(c, hipMemcpyAsync(dli, sl.lit.data(), sl.lit.size() * 2, hipMemcpyHostToDevice, c->stream));
+      HIPCHK(c, hipMemcpyAsync(dpos, posv.data(), (size_t)n * 4, hipMemcpyHostToDevice, c->stream));
+      d.pent = de;
+      d.pslice = ds;
+      d.plit = dli;
+      d.pos = dpos;
+    } else if (k == 3) {
       // compact 8-byte entries (16-bit codes: position | negated << 15,
       // n <= 32768), each position's owned clauses first, interleaved by
       // slices of 64 positions; a slice is as long as its longest list (its

@@ -473,8 +473,8 @@ hipError_t launch_restart_best(const int64_t* rbestF, const int64_t* rbestT,
 // ---- launchers (maxsat.hip) -------------------------------------------------
 
 struct SatDev {
-  const int32_t* inc_ptr;   // [n+1] per-variable incidence ranges
-  const int32_t* inc;       // entries of k int32: (k-1) other literal codes, then meta
+  const int32_t* inc_ptr;   // [n+1] per-variable incidence ranges (null with pent)
+  const int32_t* inc;       // (null with pent) entries of k int32: (k-1) other literal codes, then meta
   const int32_t* lits;      // [m][k] literal codes (var | neg<<31)
   const int32_t* w;         // [m]
   float* X;                 // [B][ld]
@@ -500,11 +500,26 @@ struct SatDev {
   // pinc_ptr[p + 1] - pinc_ptr[p]
   const uint64_t* pinc3;
   const int32_t* pinc3_slice;  // [ceil(n / 64)]
+  // satres.hip's layout (null: the formula runs on the kernels of maxsat.hip),
+  // literals coded 2 * position + plain
+  const uint32_t* pent;   // occurrences by slices of 64 positions, in groups of four
+  const int2* pslice;     // per slice {first word, full groups << 1 | a group is left over}
+  const uint16_t* plit;   // [k][m] the clauses' literals
+  const int32_t* pos;     // [n] position of a variable
   int n, m, k, ld, B;
   float ios;                // 1/s
   GdaP gp;
 };
 bool sat_fits(int n, size_t* lds_bytes);
+// ---- launchers (satres.hip)
+int satres_copies(int n, int k);          // copies of the literal table, 0: not supported
+int satres_word(int n, int c, int w);     // word of a literal in copy c
+hipError_t launch_sat_resident(const SatDev& d, int64_t t0, int nsteps, hipStream_t s);
+hipError_t launch_satres_adjoint(int mode, const SatDev& d, const float* X, int ldx, const float* Y,
+                                 const float* dL, float* dx, float* dy, int ldo, int nb,
+                                 hipStream_t s);
+hipError_t launch_satres_fwd(const SatDev& d, const float* x, const float* y, int nb, float* L,
+                             hipStream_t s);
 hipError_t launch_sat_persistent(const SatDev& d, int64_t t0, int nsteps, hipStream_t s);
 hipError_t launch_sat_grad(const SatDev& d, const float* X, int ldx, float* G, int nb,
                            hipStream_t s);

@@ -266,6 +266,7 @@ static hipError_t launch_sat_r(const SatDev& d, int64_t t0, int nsteps, hipStrea
 // the update evaluate both forms of g and g' for every coordinate.
 hipError_t launch_sat_persistent(const SatDev& d, int64_t t0, int nsteps, hipStream_t s) {
   if (nsteps <= 0) return hipSuccess;
+  if (d.pent) return launch_sat_resident(d, t0, nsteps, s);
   if (d.gp.gkind == 0)
     return d.pinc3 ? launch_sat_r<true, 0>(d, t0, nsteps, s)
                   : launch_sat_r<false, 0>(d, t0, nsteps, s);
@@ -329,6 +330,7 @@ static hipError_t launch_adjoint(int mode, const SatDev& d, const float* X, int 
                                  const float* Y, const float* dL, float* dx, float* dy, int ldo,
                                  int nb, hipStream_t s) {
   if (nb <= 0) return hipSuccess;
+  if (d.pent) return launch_satres_adjoint(mode, d, X, ldx, Y, dL, dx, dy, ldo, nb, s);
   size_t lds = 0;
   const int use_lds = sat_fits(d.n, &lds) ? 1 : 0;
   if (!use_lds) lds = 0;
@@ -402,6 +404,7 @@ __global__ void __launch_bounds__(kFwdNT)
 hipError_t launch_sat_fwd(const SatDev& d, const float* x, const float* y, int nb, float* L,
                           hipStream_t s) {
   if (nb <= 0) return hipSuccess;
+  if (d.pent) return launch_satres_fwd(d, x, y, nb, L, s);
   size_t lds = 0;
   const int use_lds = sat_fits(d.n, &lds) ? 1 : 0;
   if (!use_lds) lds = 0;
