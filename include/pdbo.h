@@ -349,7 +349,7 @@ PDBO_API pdbo_status qubo_gda_batch_result(pdbo_ctx* ctx, int32_t inst, pdbo_res
 PDBO_API pdbo_status qubo_gda_batch_solve(int32_t k, const pdbo_qubo* probs, const pdbo_params* par,
                                  int32_t T, int32_t grouped, void* stream, pdbo_result* results);
 
-/* ---- Max-k-Cut (softmax reparametrisation, row-parallel kernel) ----------- */
+/* ---- Max-k-Cut (softmax reparametrisation) -------------------------------- */
 
 /* Max-k-Cut through the softmax reparametrisation of App. B: node i of a
  * restart has logits Z_{:,i} (k reals) and probabilities X_{:,i} =
@@ -371,7 +371,10 @@ PDBO_API pdbo_status qubo_gda_batch_solve(int32_t k, const pdbo_qubo* probs, con
  * categories (nb, n) bytes in [0, k); grad returns d(Tr(X W X^T)/s)/dZ at
  * logits x, (B, n, k).  EINVAL for an asymmetric W, a diagonal entry, k out of
  * range; ERANGE for a row of |W| summing to 2^31 or more; EUNSUPPORTED for the
- * polynomial g or the scalar dual. */
+ * polynomial g or the scalar dual.  Where it is estimated faster, one workgroup
+ * runs a restart's whole step call with X in LDS (float32 X within 160 KB, |W| <= 2048;
+ * launch class PDBO_K_PERSISTENT, graph_chunk has nothing to do); the
+ * row-parallel kernels give the same bits (PDBO_KCUT_RESIDENT=0 keeps them). */
 PDBO_API pdbo_status kcut_gda_init(const pdbo_kcut* prob, const pdbo_params* par, void* stream,
                                    pdbo_ctx** out);
 
@@ -427,7 +430,8 @@ PDBO_API pdbo_status qubo_gda_trace_f64(pdbo_ctx* ctx, int32_t cap, int64_t* t, 
  *                      iteration's best of B runs in extra workgroups of the
  *                      next step launch, and only the last iteration of each
  *                      qubo_gda_step call (or graph of iterations) launches it
- *   PDBO_K_PERSISTENT  the CSR and MaxSAT persistent kernels (one per step call)
+ *   PDBO_K_PERSISTENT  the CSR, MaxSAT and Max-k-Cut persistent kernels (one per
+ *                      step call, or per 1023 iterations of it)
  *   PDBO_K_INCR        exact objective differences from the recorded rounding
  *                      changes: when at most 32 coordinates of a restart's
  *                      rounded iterate changed since the previous evaluation,

@@ -1467,6 +1467,107 @@ __global__ void put_eval_desc_kernel(InstDev* dst, InstDev v, int64_t* S, int64_
   }
 }
 
+// The layout of the resident kernels (CsrDev::rent, KcutDev::rent): entries of
+// the rows order[q] by slices of 64 positions q; a row's full groups of four
+// entries, then one group with what is left of it (one to three), each row's
+// entries in order.  Padding entries have weight 0.  off[q nc + c]: what an
+// entry carries for position q, by copy of x (nc copies); bank(off): the LDS
+// bank it reads.
+struct ResLayout {
+  std::vector<uint32_t> ent;
+  std::vector<int2> slice;
+  std::vector<int32_t> cp;
+};
+
+int64_t res_layout_words(int n, const int32_t* rp, const std::vector<int32_t>& order,
+                                std::vector<int2>* slice) {
+  int64_t tot = 0;
+  for (int s = 0; s < (n + 63) / 64; ++s) {
+    int nf = 0, rest = 0;
+    for (int q = s * 64; q < std::min(n, s * 64 + 64); ++q) {
+      const int len = rp[order[q] + 1] - rp[order[q]];
+      nf = std::max(nf, len / 4);
+      rest |= len % 4 != 0;
+    }
+    if (slice) slice->push_back(make_int2((int)tot, nf << 1 | rest));
+    tot += 256 * (int64_t)(nf + rest);
+  }
+  return tot;
+}
+
+// rows by decreasing degree (ties by index): a wave's rows then have nearly the
+// same number of entries
+std::vector<int32_t> degree_order(int n, const int32_t* rp) {
+  std::vector<int32_t> order(n);
+  for (int i = 0; i < n; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int32_t a, int32_t b) { return rp[a + 1] - rp[a] > rp[b + 1] - rp[b]; });
+  return order;
+}
+
+template <typename Bank>
+void res_layout(int n, const int32_t* rp, const int32_t* col, const int32_t* val,
+                       const std::vector<int32_t>& order, int nc, const std::vector<uint16_t>& off,
+                       Bank bank, ResLayout& L) {
+  const int64_t tot = res_layout_words(n, rp, order, &L.slice);
+  L.ent.assign((size_t)tot + 256, 0u);  // one group more: a kernel reads ahead by a group
+  std::vector<int32_t> pos(n);
+  for (int q = 0; q < n; ++q) pos[order[q]] = q;
+  for (size_t s = 0; s < L.slice.size(); ++s) {
+    const int nf = L.slice[s].y >> 1, ng = nf + (L.slice[s].y & 1);
+    for (int k = 0; k < 4 * ng; ++k) {  // the wave's gather k: entry k % 4 of group k / 4
+      uint32_t* to = &L.ent[(size_t)L.slice[s].x + 256 * (size_t)(k / 4) + k % 4];
+      for (int half = 0; half < 2; ++half) {
+        // A gather takes as many cycles as the fullest of the 32 banks has
+        // addresses, for each half of the wave: every lane takes the copy whose
+        // bank is the emptiest so far.  Lanes without an entry repeat an
+        // address of the half (a broadcast, no cycle of its own).
+        int load[32] = {};
+        int some = -1;
+        int32_t pick[32];
+        for (int l = 0; l < 32; ++l) {
+          pick[l] = -1;
+          const int q = (int)s * 64 + half * 32 + l;
+          if (q >= n) continue;
+          const int b = rp[order[q]], len = rp[order[q] + 1] - b;
+          // left-over entries are in the slice's last group whatever the row's own full groups
+          const int e = k < 4 * nf ? (k < len / 4 * 4 ? k : -1)
+                                   : (k - 4 * nf < len % 4 ? len / 4 * 4 + k - 4 * nf : -1);
+          if (e < 0) continue;
+          const uint16_t* o = &off[(size_t)pos[col[b + e]] * nc];
+          int best = 0;
+          for (int c = 1; c < nc; ++c)
+            if (load[bank(o[c])] < load[bank(o[best])]) best = c;
+          ++load[bank(o[best])];
+          const _Float16 w = (_Float16)(float)val[b + e];
+          uint16_t wb;
+          std::memcpy(&wb, &w, 2);
+          to[4 * (half * 32 + l)] = (uint32_t)o[best] | ((uint32_t)wb << 16);
+          pick[l] = o[best];
+          some = o[best];
+        }
+        if (some < 0) continue;
+        for (int l = 0; l < 32; ++l)
+          if (pick[l] < 0) to[4 * (half * 32 + l)] = (uint32_t)some;
+      }
+    }
+  }
+}
+
+// resident.hip's: byte offsets, c' by position, slices up to the compiled size
+void csr_res_layout(const CsrCanon& C, const std::vector<int32_t>& order, ResLayout& L) {
+  const int n = C.n, np = csr_resident_rows(n) * 1024, nc = csr_resident_copies(n);
+  std::vector<uint16_t> off((size_t)nc * n);
+  L.cp.assign(np, 0);
+  for (int q = 0; q < n; ++q) {
+    L.cp[q] = (int32_t)C.cp[order[q]];
+    for (int c = 0; c < nc; ++c) off[(size_t)q * nc + c] = (uint16_t)(4 * csr_resident_word(n, c, q));
+  }
+  res_layout(n, C.rp.data(), C.col.data(), C.val.data(), order, nc, off,
+             [](uint16_t o) { return o / 4 % 32; }, L);
+  L.slice.resize(np / 64, make_int2(0, 0));
+}
+
 }  // namespace
 
 // =================================================================== ABI
@@ -1579,87 +1680,6 @@ static pdbo_status persistent_supported(const pdbo_params* p) {
 static pdbo_status spmm_init(const CsrCanon* C, const RealCanon* R, const pdbo_params* p,
                              void* stream, pdbo_ctx** out);
 
-// The layout of the resident kernel (CsrDev::rent): entries of the rows
-// order[q] by slices of 64 positions q; a row's full groups of four entries,
-// then one group with what is left of it (one to three), each row's entries in
-// order.  Padding entries have weight 0.
-struct ResLayout {
-  std::vector<uint32_t> ent;
-  std::vector<int2> slice;
-  std::vector<int32_t> cp;
-};
-
-static int64_t res_layout_words(const CsrCanon& C, const std::vector<int32_t>& order,
-                                std::vector<int2>* slice) {
-  const int n = C.n;
-  int64_t tot = 0;
-  for (int s = 0; s < (n + 63) / 64; ++s) {
-    int nf = 0, rest = 0;
-    for (int q = s * 64; q < std::min(n, s * 64 + 64); ++q) {
-      const int len = C.rp[order[q] + 1] - C.rp[order[q]];
-      nf = std::max(nf, len / 4);
-      rest |= len % 4 != 0;
-    }
-    if (slice) slice->push_back(make_int2((int)tot, nf << 1 | rest));
-    tot += 256 * (int64_t)(nf + rest);
-  }
-  return tot;
-}
-
-static void res_layout(const CsrCanon& C, const std::vector<int32_t>& order, ResLayout& L) {
-  const int n = C.n, np = csr_resident_rows(n) * 1024, nc = csr_resident_copies(n);
-  const int64_t tot = res_layout_words(C, order, &L.slice);
-  L.ent.assign((size_t)std::max<int64_t>(tot, 4), 0u);
-  L.cp.assign(np, 0);
-  std::vector<int32_t> pos(n);
-  std::vector<uint16_t> off((size_t)nc * n);  // byte offsets by position and copy
-  for (int q = 0; q < n; ++q) {
-    pos[order[q]] = q;
-    L.cp[q] = (int32_t)C.cp[order[q]];
-    for (int c = 0; c < nc; ++c) off[(size_t)q * nc + c] = (uint16_t)(4 * csr_resident_word(n, c, q));
-  }
-  for (size_t s = 0; s < L.slice.size(); ++s) {
-    const int nf = L.slice[s].y >> 1, ng = nf + (L.slice[s].y & 1);
-    for (int k = 0; k < 4 * ng; ++k) {  // the wave's gather k: entry k % 4 of group k / 4
-      uint32_t* to = &L.ent[(size_t)L.slice[s].x + 256 * (size_t)(k / 4) + k % 4];
-      for (int half = 0; half < 2; ++half) {
-        // A gather takes as many cycles as the fullest of the 32 banks has
-        // addresses, for each half of the wave: every lane takes the copy whose
-        // bank is the emptiest so far.  Lanes without an entry repeat an
-        // address of the half (a broadcast, no cycle of its own).
-        int load[32] = {};
-        int some = -1;
-        int32_t pick[32];
-        for (int l = 0; l < 32; ++l) {
-          pick[l] = -1;
-          const int q = (int)s * 64 + half * 32 + l;
-          if (q >= n) continue;
-          const int b = C.rp[order[q]], len = C.rp[order[q] + 1] - b;
-          // left-over entries are in the slice's last group whatever the row's own full groups
-          const int e = k < 4 * nf ? (k < len / 4 * 4 ? k : -1)
-                                   : (k - 4 * nf < len % 4 ? len / 4 * 4 + k - 4 * nf : -1);
-          if (e < 0) continue;
-          const uint16_t* o = &off[(size_t)pos[C.col[b + e]] * nc];
-          int best = 0;
-          for (int c = 1; c < nc; ++c)
-            if (load[o[c] / 4 % 32] < load[o[best] / 4 % 32]) best = c;
-          ++load[o[best] / 4 % 32];
-          const _Float16 w = (_Float16)(float)C.val[b + e];
-          uint16_t wb;
-          std::memcpy(&wb, &w, 2);
-          to[4 * (half * 32 + l)] = (uint32_t)o[best] | ((uint32_t)wb << 16);
-          pick[l] = o[best];
-          some = o[best];
-        }
-        if (some < 0) continue;
-        for (int l = 0; l < 32; ++l)
-          if (pick[l] < 0) to[4 * (half * 32 + l)] = (uint32_t)some;
-      }
-    }
-  }
-  L.slice.resize(np / 64, make_int2(0, 0));
-}
-
 static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stream, pdbo_ctx** out) {
   if (p->eval_every != 1) return fail(nullptr, PDBO_EUNSUPPORTED, "the CSR path evaluates every iteration");
   if (p->tile > PDBO_CSR_ROWS)
@@ -1677,19 +1697,13 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
   const int64_t lim32 = int64_t(1) << 31;
   const bool small32 = 512 * C.rowabs < lim32 && 512 * cmax < lim32;
   const bool tot32 = small32 && (int64_t)n * C.rowabs < lim32 && (int64_t)n * cmax < lim32;
-  // rows by decreasing degree (ties by index): a wave's rows then have nearly
-  // the same number of entries
-  std::vector<int32_t> order(n);
-  for (int i = 0; i < n; ++i) order[i] = i;
-  std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-    return C.rp[a + 1] - C.rp[a] > C.rp[b + 1] - C.rp[b];
-  });
+  const std::vector<int32_t> order = degree_order(n, C.rp.data());
   // resident.hip: weights exact in float16, twice a row's sum exact in float32,
   // totals in int32, positions within a 16-bit byte offset
   const bool res_ok = C.amax <= 2048 && C.rowabs < (1 << 23) && tot32 && csr_resident_rows(n) > 0 &&
                       n <= 16384 && persistent_ok(p);
   const bool few = path == PDBO_CSR_AUTO && p->B < kResidentMinB;
-  const int64_t res_words = res_ok ? res_layout_words(C, order, nullptr) : 0;
+  const int64_t res_words = res_ok ? res_layout_words(n, C.rp.data(), order, nullptr) : 0;
   bool seq = false;
   if (path == PDBO_CSR_AUTO) {
     if (fits && p->B >= kResidentMinB && persistent_ok(p)) {
@@ -1796,7 +1810,7 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
       }
     }
     if (seq || two_sums) {
-      res_layout(C, order, rl);
+      csr_res_layout(C, order, rl);
       uint32_t* re = nullptr;
       int2* rs = nullptr;
       int32_t* rc = nullptr;
@@ -2291,11 +2305,13 @@ pdbo_status qubo_gda_step(pdbo_ctx* c, int32_t nsteps) {
   }
   if (c->kind == 0) return dense_steps(c, nsteps);
   if (c->kind == 3) return rowpar_steps(c, nsteps, spmm_one_step);
-  if (c->kind == 4) return rowpar_steps(c, nsteps, kcut_one_step);
+  if (c->kind == 4 && !c->kcut.rent) return rowpar_steps(c, nsteps, kcut_one_step);
   TimedLaunch tl;
   t_begin(c, tl, PDBO_K_PERSISTENT);
   if (c->kind == 1)
     HIPCHK(c, launch_csr_persistent(c->csr, c->compact, c->t_host, nsteps, c->stream));
+  else if (c->kind == 4)
+    HIPCHK(c, launch_kcut_resident(c->kcut, nsteps, c->stream));
   else
     HIPCHK(c, launch_sat_persistent(c->sat, c->t_host, nsteps, c->stream));
   t_end(c, tl);
@@ -2400,8 +2416,14 @@ pdbo_status qubo_gda_get_state(pdbo_ctx* c, float* x, float* y, int64_t* t) {
   if (c->kind == 0 && c->insts_h.size() != 1) return fail(c, PDBO_ESTATE, "batched context");
   if (c->kind == 4) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    if (x) STCHK(kcut_download(c, c->kcut.Z, x, c->kcut.k));
-    if (y) STCHK(kcut_download(c, c->kcut.Y, y, 1));
+    if (c->kcut.rent) {  // restart-major
+      const size_t ty = (size_t)c->B * c->kcut.n;
+      if (x) HIPCHK(c, hipMemcpy(x, c->kcut.Z, ty * c->kcut.k * sizeof(float), hipMemcpyDeviceToHost));
+      if (y) HIPCHK(c, hipMemcpy(y, c->kcut.Y, ty * sizeof(float), hipMemcpyDeviceToHost));
+    } else {
+      if (x) STCHK(kcut_download(c, c->kcut.Z, x, c->kcut.k));
+      if (y) STCHK(kcut_download(c, c->kcut.Y, y, 1));
+    }
     if (t) *t = c->t_host;
     return PDBO_OK;
   }
@@ -2446,7 +2468,10 @@ pdbo_status qubo_gda_set_state(pdbo_ctx* c, const float* x, const float* y, int6
       for (size_t i = 0; i < ty; ++i)
         if (!std::isfinite(y[i])) return fail(c, PDBO_EINVAL, "y must be finite");
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    if (x) {
+    if (d.rent) {  // restart-major; X = softmax(Z) is formed by the next call
+      if (x) HIPCHK(c, hipMemcpy(d.Z, x, tz * sizeof(float), hipMemcpyHostToDevice));
+      if (y) HIPCHK(c, hipMemcpy(d.Y, y, ty * sizeof(float), hipMemcpyHostToDevice));
+    } else if (x) {
       TempDev tx, tyd;
       STCHK(temp_upload(c, tx, x, tz * sizeof(float)));
       if (y) STCHK(temp_upload(c, tyd, y, ty * sizeof(float)));
@@ -2520,7 +2545,13 @@ pdbo_status qubo_gda_restart(pdbo_ctx* c, const double* x0) {
     TempDev t;
     STCHK(upload_x0(c, t, x0, tz));
     c->parity = 0;
-    HIPCHK(c, launch_kcut_init((const double*)t.p, d, (float)c->par.y0, c->par.seed, c->stream));
+    if (d.rent) {
+      HIPCHK(c, launch_kcut_resident_init((const double*)t.p, d, (float)c->par.y0, c->par.seed, c->stream));
+      HIPCHK(c, launch_fill_i64(d.rbestF, kI64Max, B, c->stream));
+      HIPCHK(c, launch_fill_i64(d.rbestT, kI64Max, B, c->stream));
+    } else {
+      HIPCHK(c, launch_kcut_init((const double*)t.p, d, (float)c->par.y0, c->par.seed, c->stream));
+    }
     const int64_t zero = 0;
     Incumbent init{kI64Max, -1, -1, 0};
     HIPCHK(c, hipMemcpyAsync(d.t_dev, &zero, sizeof(zero), hipMemcpyHostToDevice, c->stream));
@@ -3053,11 +3084,27 @@ static pdbo_status check_kcut(const pdbo_kcut* g, const pdbo_params* p) {
   return PDBO_OK;
 }
 
+// Estimated iteration of the two Max-k-Cut paths, fitted to (us, resident against
+// row-parallel): n = 1000, degree 4, k = 3: B = 1 2.7 / 11, B = 100 3.0 / 20;
+// n = 10^4, degree 4, k = 3: B = 1 14.7 / 13, B = 100 15.3 / 41, B = 300 32 / 90;
+// n = 4000, degree 8, k = 8: B = 10 21.5 / 40; degree 100, k = 3: n = 1000,
+// B = 10 13 / 42; n = 5000, B = 10 54 / 42, B = 100 55 / 132.  The restarts' own
+// records (32 KB each) bound B.
+constexpr int kKcutResidentMaxB = 1024;
+static double kcut_resident_us(int n, int k, int B, int64_t words) {
+  return ((B + 255) / 256) * (1.5 + 2.7e-4 * (1 + k) * n + 2.9e-5 * k * (double)words);
+}
+static double kcut_rows_us(int n, int k, int B, int64_t nnz) {
+  return 11.0 + 0.09 * B + 7e-6 * (double)n * k * B + 0.3 * (double)nnz / n;
+}
+
 pdbo_status kcut_gda_init(const pdbo_kcut* g, const pdbo_params* p, void* stream, pdbo_ctx** out) {
   if (!out) return fail(nullptr, PDBO_EINVAL, "out is NULL");
   *out = nullptr;
   STCHK(check_kcut(g, p));
   const int n = g->n, B = p->B, k = g->k;
+  std::vector<int32_t> order;  // host staging, alive until init syncs
+  ResLayout rl;
   pdbo_ctx* c = new pdbo_ctx();
   c->kind = 4;
   c->n_of.push_back(n);
@@ -3091,10 +3138,50 @@ pdbo_status kcut_gda_init(const pdbo_kcut* g, const pdbo_params* p, void* stream
     d.w = w;
     const size_t sz = (size_t)n * B * k;
     STCHK(dalloc(c, &d.Z, sz));
-    STCHK(dalloc(c, &d.X[0], sz));
-    STCHK(dalloc(c, &d.X[1], sz));
     STCHK(dalloc(c, &d.Y, (size_t)n * B));
-    STCHK(dalloc(c, &d.part, (size_t)d.grid * d.W));
+    int32_t wmax = 0;
+    for (int64_t e = 0; e < nnz; ++e) wmax = std::max(wmax, g->w[e] < 0 ? -g->w[e] : g->w[e]);
+    // kcutres.hip takes the instance when X fits in LDS, the weights are exact in
+    // float16 and it is estimated faster (PDBO_KCUT_RESIDENT=0 keeps the
+    // row-parallel kernels, 1 leaves the estimate out)
+    const int nc = kcutres_copies(n, k);
+    const char* res_env = std::getenv("PDBO_KCUT_RESIDENT");
+    bool res = nc > 0 && wmax <= 2048 && B <= kKcutResidentMaxB && !(res_env && std::atoi(res_env) == 0);
+    if (res) {
+      order = degree_order(n, g->row_ptr);
+      res = (res_env && std::atoi(res_env) == 1) || kcut_resident_us(n, k, B, res_layout_words(n, g->row_ptr, order, nullptr)) <
+            kcut_rows_us(n, k, B, nnz);
+    }
+    if (res) {
+      std::vector<uint16_t> off((size_t)nc * n);
+      for (int q = 0; q < n; ++q)
+        for (int cc = 0; cc < nc; ++cc) off[(size_t)q * nc + cc] = (uint16_t)kcutres_word(n, k, cc, q);
+      res_layout(n, g->row_ptr, g->col_idx, g->w, order, nc, off, [](uint16_t o) { return o % 32; }, rl);
+      uint32_t* re = nullptr;
+      int2* rs = nullptr;
+      int32_t* ro = nullptr;
+      STCHK(dalloc(c, &re, rl.ent.size()));
+      STCHK(dalloc(c, &rs, rl.slice.size()));
+      STCHK(dalloc(c, &ro, n));
+      HIPCHK(c, hipMemcpyAsync(re, rl.ent.data(), rl.ent.size() * 4, hipMemcpyHostToDevice, c->stream));
+      HIPCHK(c, hipMemcpyAsync(rs, rl.slice.data(), rl.slice.size() * sizeof(int2), hipMemcpyHostToDevice,
+                               c->stream));
+      HIPCHK(c, hipMemcpyAsync(ro, order.data(), (size_t)n * 4, hipMemcpyHostToDevice, c->stream));
+      d.rent = re;
+      d.rslice = rs;
+      d.order = ro;
+      STCHK(dalloc(c, &d.rbestF, B));
+      STCHK(dalloc(c, &d.rbestT, B));
+      STCHK(dalloc(c, &d.best_xr, (size_t)B * n));
+      STCHK(dalloc(c, &d.rtr, (size_t)B * kResTrace));
+      STCHK(dalloc(c, &d.rtl, B));
+      HIPCHK(c, launch_fill_i64(d.rbestF, kI64Max, B, c->stream));
+      HIPCHK(c, launch_fill_i64(d.rbestT, kI64Max, B, c->stream));
+    } else {
+      STCHK(dalloc(c, &d.X[0], sz));
+      STCHK(dalloc(c, &d.X[1], sz));
+      STCHK(dalloc(c, &d.part, (size_t)d.grid * d.W));
+    }
     STCHK(dalloc(c, &d.Flast, B));
     STCHK(dalloc(c, &d.inc, 1));
     STCHK(dalloc(c, &d.best_x, n));
@@ -3108,7 +3195,10 @@ pdbo_status kcut_gda_init(const pdbo_kcut* g, const pdbo_params* p, void* stream
     HIPCHK(c, launch_fill_i32(d.win, -1, 1, c->stream));
     TempDev t;
     STCHK(upload_x0(c, t, p->x0, (size_t)B * n * k));
-    HIPCHK(c, launch_kcut_init((const double*)t.p, d, (float)p->y0, p->seed, c->stream));
+    if (d.rent)
+      HIPCHK(c, launch_kcut_resident_init((const double*)t.p, d, (float)p->y0, p->seed, c->stream));
+    else
+      HIPCHK(c, launch_kcut_init((const double*)t.p, d, (float)p->y0, p->seed, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return PDBO_OK;
   };

@@ -227,6 +227,47 @@ __device__ __forceinline__ int64_t row16_sum_i64(int64_t v) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+// ---- Max-k-Cut: one node's categories ----------------------------------------
+
+template <int K>
+__device__ __forceinline__ int argmax_k(const float (&x)[K]) {
+  int c = 0;
+#pragma unroll
+  for (int u = 1; u < K; ++u)
+    if (x[u] > x[c]) c = u;
+  return c;
+}
+
+template <int K>
+__device__ __forceinline__ void softmax_k(const float (&z)[K], float (&x)[K]) {
+  float m = z[0];
+#pragma unroll
+  for (int u = 1; u < K; ++u) m = fmaxf(m, z[u]);
+  float t = 0.f;
+#pragma unroll
+  for (int u = 0; u < K; ++u) {
+    x[u] = expf(z[u] - m);
+    t += x[u];
+  }
+  const float r = 1.f / t;
+#pragma unroll
+  for (int u = 0; u < K; ++u) x[u] *= r;
+}
+
+// g of one node's probabilities and its partial derivatives
+template <int GK, int K>
+__device__ __forceinline__ float kg_value(const float (&x)[K]) {
+  float v = 0.f;
+#pragma unroll
+  for (int u = 0; u < K; ++u) v += GK == 0 ? x[u] * x[u] : (x[u] > 0.f ? x[u] * logf(x[u]) : 0.f);
+  return GK == 0 ? v - 1.f : v;
+}
+
+template <int GK>
+__device__ __forceinline__ float kg_deriv(float x) {
+  return GK == 0 ? 2.f * x : logf(fmaxf(x, kEntropyEps)) + 1.f;
+}
+
 // ---- launchers (dense.hip) --------------------------------------------------
 
 constexpr int kFlipMax = 32;
@@ -336,6 +377,12 @@ constexpr int kResTrace = 1024;  // records per restart and launch
 int csr_resident_rows(int n);    // positions per thread, 0 when n is too large
 int csr_resident_copies(int n);  // copies of x in LDS
 int csr_resident_word(int n, int c, int p);  // word of position p in copy c
+// Incumbent and trace from the restarts' own improvements in a launch of nsteps
+// iterations; advances *t_dev.
+hipError_t launch_resident_merge(const TraceRec* rtr, const int32_t* rtl, int B, int n,
+                                 const uint8_t* best_xr, Incumbent* inc, uint8_t* best_x,
+                                 TraceRec* trace, int32_t* trace_len, int trace_cap, int64_t* t_dev,
+                                 int nsteps, hipStream_t s);
 hipError_t launch_csr_resident(const CsrDev& d, int64_t t0, int nsteps, hipStream_t s);
 hipError_t launch_csr_grad(const CsrDev& d, const float* X, float* G, int nb, hipStream_t s);
 hipError_t launch_csr_eval(const CsrDev& d, const int8_t* xr, int nb, int64_t* F, hipStream_t s);
@@ -443,7 +490,24 @@ struct KcutDev {
   int W, G, nslices, grid;
   float tos;              // 2 / s
   GdaP gp;
+  // kcutres.hip (null: the instance runs on the row-parallel kernels): Z [B][n][k]
+  // and Y [B][n] are then restart-major and X is not kept in memory
+  const uint32_t* rent;   // entries by slices of 64 positions, as CsrDev::rent: {first
+                          // word of X_j | float16 weight << 16}
+  const int2* rslice;     // per slice {first word, full groups << 1 | left-over group}
+  const int32_t* order;   // [n] node at a position
+  int64_t* rbestF;        // [B] the restarts' own bests
+  int64_t* rbestT;
+  uint8_t* best_xr;       // [B][n] categories
+  TraceRec* rtr;          // [B][kResTrace] and their number: improvements in one launch
+  int32_t* rtl;
 };
+// ---- launchers (kcutres.hip)
+int kcutres_copies(int n, int k);  // copies of X in LDS, 0: not supported
+int kcutres_word(int n, int k, int c, int p);  // first word of position p in copy c
+hipError_t launch_kcut_resident(const KcutDev& d, int nsteps, hipStream_t s);
+hipError_t launch_kcut_resident_init(const double* z0, const KcutDev& d, float y0, uint64_t seed,
+                                     hipStream_t s);
 hipError_t launch_kcut(const KcutDev& d, int mode, int parity, float* G, hipStream_t s);
 hipError_t launch_kcut_best(const KcutDev& d, int parity, int advance, hipStream_t s);
 hipError_t launch_kcut_init(const double* z0, const KcutDev& d, float y0, uint64_t seed,

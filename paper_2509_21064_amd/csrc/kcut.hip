@@ -25,45 +25,6 @@ namespace pdbo {
 constexpr int kKcutThreads = 256;
 constexpr int kKcutUnroll = 4;  // neighbours whose loads are in flight together
 
-template <int K>
-__device__ __forceinline__ int argmax_k(const float (&x)[K]) {
-  int c = 0;
-#pragma unroll
-  for (int u = 1; u < K; ++u)
-    if (x[u] > x[c]) c = u;
-  return c;
-}
-
-template <int K>
-__device__ __forceinline__ void softmax_k(const float (&z)[K], float (&x)[K]) {
-  float m = z[0];
-#pragma unroll
-  for (int u = 1; u < K; ++u) m = fmaxf(m, z[u]);
-  float t = 0.f;
-#pragma unroll
-  for (int u = 0; u < K; ++u) {
-    x[u] = expf(z[u] - m);
-    t += x[u];
-  }
-  const float r = 1.f / t;
-#pragma unroll
-  for (int u = 0; u < K; ++u) x[u] *= r;
-}
-
-// g of one node's probabilities and its partial derivatives
-template <int GK, int K>
-__device__ __forceinline__ float kg_value(const float (&x)[K]) {
-  float v = 0.f;
-#pragma unroll
-  for (int u = 0; u < K; ++u) v += GK == 0 ? x[u] * x[u] : (x[u] > 0.f ? x[u] * logf(x[u]) : 0.f);
-  return GK == 0 ? v - 1.f : v;
-}
-
-template <int GK>
-__device__ __forceinline__ float kg_deriv(float x) {
-  return GK == 0 ? 2.f * x : logf(fmaxf(x, kEntropyEps)) + 1.f;
-}
-
 // MODE 0: gradient, the update of (Z, X, Y) and the objective of round(X^t);
 // MODE 1: the objective only; MODE 2: the gradient of f/s with respect to Z
 // into Gout (node-major).

@@ -565,6 +565,15 @@ __global__ void __launch_bounds__(kMergeThreads)
   if (tid == 0) *t_dev = t0 + nsteps;
 }
 
+hipError_t launch_resident_merge(const TraceRec* rtr, const int32_t* rtl, int B, int n,
+                                 const uint8_t* best_xr, Incumbent* inc, uint8_t* best_x,
+                                 TraceRec* trace, int32_t* trace_len, int trace_cap, int64_t* t_dev,
+                                 int nsteps, hipStream_t s) {
+  hipLaunchKernelGGL(resident_merge_kernel, dim3(1), dim3(kMergeThreads), 0, s, rtr, rtl, B, n, best_xr,
+                     inc, best_x, trace, trace_len, trace_cap, t_dev, nsteps);
+  return hipGetLastError();
+}
+
 hipError_t launch_csr_resident(const CsrDev& d, int64_t t0, int nsteps, hipStream_t s) {
   // a launch has at most one record per iteration (the starting state's among
   // them) and restart: calls are cut so that these fit
@@ -573,9 +582,8 @@ hipError_t launch_csr_resident(const CsrDev& d, int64_t t0, int nsteps, hipStrea
     hipError_t e = d.gp.gkind == 0 ? launch_res<0>(d, t0 + done, k, s) : launch_res<1>(d, t0 + done, k, s);
     if (e != hipSuccess) return e;
     if (d.rtr) {
-      hipLaunchKernelGGL(resident_merge_kernel, dim3(1), dim3(kMergeThreads), 0, s, d.rtr, d.rtl, d.B, d.n,
-                         d.best_xr, d.inc, d.best_x, d.trace, d.trace_len, d.trace_cap, d.t_dev, k);
-      e = hipGetLastError();
+      e = launch_resident_merge(d.rtr, d.rtl, d.B, d.n, d.best_xr, d.inc, d.best_x, d.trace, d.trace_len,
+                                d.trace_cap, d.t_dev, k, s);
       if (e != hipSuccess) return e;
     }
     done += k;
