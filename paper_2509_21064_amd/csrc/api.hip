@@ -97,6 +97,10 @@ struct pdbo_ctx {
   std::vector<TileDev> tiles_h;
   TileDev* tiles_d = nullptr;
   std::vector<int> tile_off, tile_cnt;
+  int frag = -1;  // step launches: one-wave tiles of this configuration (dense_frag), -1: cfg's tiles
+  std::vector<TileDev> frag_tiles_h;
+  TileDev* frag_tiles_d = nullptr;
+  std::vector<int> frag_off, frag_cnt;
   // incremental evaluation: one workgroup per (instance, restart), in instance order
   int2* incr_work_d = nullptr;
   std::vector<int> incr_off;  // first work item of each instance, plus the total
@@ -111,7 +115,8 @@ struct pdbo_ctx {
   // rounding, per-row terms and the result; per-restart records of the
   // resident CSR kernel and the partial sums of the row-parallel one
   float *cert_x = nullptr, *cert_y = nullptr;
-  uint8_t* cert_xs = nullptr;
+  uint8_t *cert_xs = nullptr, *cert_xf = nullptr;
+  TileDev* cert_tiles = nullptr;
   int8_t* cert_xr = nullptr;
   double *cert_rows = nullptr, *cert_res = nullptr;
   int64_t *cert_i64 = nullptr;
@@ -653,30 +658,57 @@ int32_t f32_bits(float v) {
 int element_bytes(int prec) { return prec == PDBO_FP32 ? 4 : prec == PDBO_BF16 ? 2 : 1; }
 static_assert((int)PDBO_I8 == (int)P_I8, "ABI and kernel precision codes agree");
 
-// Estimated cost of a tile configuration for a set of instances: the launch
-// runs in ceil(tiles / (256 CUs x workgroups per CU)) rounds, each costing the
-// per-CU output area, inflated when the wave tile needs more LDS bytes per MFMA
-// than the LDS can deliver at the MFMA rate (wave tiles below 64x64).
+// Estimated cost of a tile configuration for a set of instances: the fullest
+// CU's output area, inflated when the wave tile needs more LDS bytes per MFMA
+// than the LDS can deliver at the MFMA rate (wave tiles below 64x64).  Tiles
+// that share a CU count one by one: what several workgroups there would
+// overlap is small beside CUs left without a tile (us an iteration past the
+// first 64, 64x64 against 128x128: n = 200, B = 16 fp32 10.0 / 23.2; n = 3001,
+// B = 100 bf16 21.1 / 34.6; n = 1000, B = 256 int8 12.0 / 20.8; n = 5000,
+// B = 100 int8 21.0 / 34.4).
 double cfg_cost(int cfg, const std::vector<int>& ns, int B) {
   const TileCfgInfo& cf = dense_cfg(cfg);
-  const int lds = cf.dma ? 3 * (cf.BM + cf.BN) * 128 : 2 * (cf.BM + cf.BN) * 144;
-  const int occ = std::max(1, std::min(4, (160 * 1024) / lds));
   double tiles = 0;
   for (int n : ns) tiles += (double)((n + cf.BM - 1) / cf.BM) * ((B + cf.BN - 1) / cf.BN);
-  const double rounds = std::ceil(tiles / (256.0 * occ));
   const double fm = cf.BM / cf.WM / 16.0, fn = cf.BN / cf.WN / 16.0;
   const double lds_per_mfma = (fm + fn) / (fm * fn);
   const double ineff = std::max(1.0, lds_per_mfma / 0.5);
-  return rounds * occ * cf.BM * cf.BN * ineff;
+  return std::ceil(tiles / 256.0) * cf.BM * cf.BN * ineff;
 }
 
-int default_cfg(const std::vector<int>& ns, int B) {
-  // small tiles first so that they win ties on small problems
+// The main loops of the register-staged and of the direct-to-LDS tiles add the
+// products of a K chunk in different orders.  Which of the two a shape gets is
+// decided by this older estimate alone, so that a float run keeps its bits:
+// launches in rounds of as many workgroups as the chip holds.
+bool default_dma(const std::vector<int>& ns, int B) {
   static const int order[] = {1, 9, 0, 7, 2, 8, 3, 4, 6, 5};
   int best = 1;
   double bc = 1e300;
   for (int id : order) {
-    if (id >= dense_num_cfgs()) continue;
+    const TileCfgInfo& cf = dense_cfg(id);
+    const int lds = cf.dma ? 3 * (cf.BM + cf.BN) * 128 : 2 * (cf.BM + cf.BN) * 144;
+    const int occ = std::max(1, std::min(4, (160 * 1024) / lds));
+    double tiles = 0;
+    for (int n : ns) tiles += (double)((n + cf.BM - 1) / cf.BM) * ((B + cf.BN - 1) / cf.BN);
+    const double fm = cf.BM / cf.WM / 16.0, fn = cf.BN / cf.WN / 16.0;
+    const double cst = std::ceil(tiles / (256.0 * occ)) * occ * cf.BM * cf.BN *
+                       std::max(1.0, (fm + fn) / (fm * fn) / 0.5);
+    if (cst < bc) {
+      bc = cst;
+      best = id;
+    }
+  }
+  return dense_cfg(best).dma != 0;
+}
+
+int default_cfg(const std::vector<int>& ns, int B) {
+  const bool dma = default_dma(ns, B);
+  // small tiles first so that they win ties on small problems
+  static const int order[] = {1, 9, 0, 7, 2, 8, 3, 4, 6, 5};
+  int best = dma ? 9 : 1;
+  double bc = 1e300;
+  for (int id : order) {
+    if ((dense_cfg(id).dma != 0) != dma) continue;
     const double cst = cfg_cost(id, ns, B);
     if (cst < bc) {
       bc = cst;
@@ -873,11 +905,9 @@ pdbo_status setup_dense_instance(pdbo_ctx* c, const DenseCanon& C, const pdbo_pa
 // sharing one block of Ahat rows run on the same XCD, back to back, and reuse
 // that block from the XCD's L2.  PDBO_TILE_ORDER=1 selects plain row-group
 // order instead (for measurement).
-void build_tiles(pdbo_ctx* c) {
-  const TileCfgInfo& cf = dense_cfg(c->cfg);
-  c->tiles_h.clear();
-  c->tile_off.clear();
-  c->tile_cnt.clear();
+void tile_table(const std::vector<InstDev>& insts, int BM, int BN, std::vector<TileDev>& tiles,
+                std::vector<int>& off, std::vector<int>& cnt) {
+  tiles.clear();
   static const int order = [] {
     const char* e = std::getenv("PDBO_TILE_ORDER");
     return e ? std::atoi(e) : 0;
@@ -886,28 +916,28 @@ void build_tiles(pdbo_ctx* c) {
   // tile's work is proportional to its instance's n (its K loop), and the
   // grouped launch hands tiles to the CUs in list order, so the long tiles
   // start first and the short ones fill in behind them.
-  const int ninst = (int)c->insts_h.size();
+  const int ninst = (int)insts.size();
   std::vector<int> by_cost(ninst);
   for (int k = 0; k < ninst; ++k) by_cost[k] = k;
   std::stable_sort(by_cost.begin(), by_cost.end(),
-                   [&](int a, int b) { return c->insts_h[a].n > c->insts_h[b].n; });
-  c->tile_off.assign(ninst, 0);
-  c->tile_cnt.assign(ninst, 0);
+                   [&](int a, int b) { return insts[a].n > insts[b].n; });
+  off.assign(ninst, 0);
+  cnt.assign(ninst, 0);
   for (int k : by_cost) {
-    InstDev& I = c->insts_h[k];
-    I.mblocks = (I.n + cf.BM - 1) / cf.BM;
-    const int nb = (I.B + cf.BN - 1) / cf.BN;
+    const InstDev& I = insts[k];
+    const int mblocks = (I.n + BM - 1) / BM;
+    const int nb = (I.B + BN - 1) / BN;
     if (order == 1) {
-      c->tile_off[k] = (int)c->tiles_h.size();
-      for (int m = 0; m < I.mblocks; ++m)
-        for (int j = 0; j < nb; ++j) c->tiles_h.push_back(TileDev{(int)k, m * cf.BM, j * cf.BN, m});
-      c->tile_cnt[k] = (int)c->tiles_h.size() - c->tile_off[k];
+      off[k] = (int)tiles.size();
+      for (int m = 0; m < mblocks; ++m)
+        for (int j = 0; j < nb; ++j) tiles.push_back(TileDev{(int)k, m * BM, j * BN, m});
+      cnt[k] = (int)tiles.size() - off[k];
       continue;
     }
     std::vector<std::vector<TileDev>> q(8);
-    for (int m = 0; m < I.mblocks; ++m)
-      for (int j = 0; j < nb; ++j) q[m % 8].push_back(TileDev{(int)k, m * cf.BM, j * cf.BN, m});
-    c->tile_off[k] = (int)c->tiles_h.size();
+    for (int m = 0; m < mblocks; ++m)
+      for (int j = 0; j < nb; ++j) q[m % 8].push_back(TileDev{(int)k, m * BM, j * BN, m});
+    off[k] = (int)tiles.size();
     size_t longest = 0;
     for (auto& v : q) longest = std::max(longest, v.size());
     std::vector<TileDev> rest;
@@ -917,14 +947,91 @@ void build_tiles(pdbo_ctx* c) {
       for (auto& v : q) {
         if (r >= v.size()) continue;
         if (full)
-          c->tiles_h.push_back(v[r]);
+          tiles.push_back(v[r]);
         else
           rest.push_back(v[r]);
       }
     }
-    c->tiles_h.insert(c->tiles_h.end(), rest.begin(), rest.end());
-    c->tile_cnt[k] = (int)c->tiles_h.size() - c->tile_off[k];
+    tiles.insert(tiles.end(), rest.begin(), rest.end());
+    cnt[k] = (int)tiles.size() - off[k];
   }
+}
+
+void build_tiles(pdbo_ctx* c) {
+  const TileCfgInfo& cf = dense_cfg(c->cfg);
+  for (InstDev& I : c->insts_h) I.mblocks = (I.n + cf.BM - 1) / cf.BM;
+  tile_table(c->insts_h, cf.BM, cf.BN, c->tiles_h, c->tile_off, c->tile_cnt);
+}
+
+// The operand shadow in fragment order, from the iterate of X[parity] / Xs[parity].
+pdbo_status frag_shadow(pdbo_ctx* c) {
+  if (c->frag < 0) return PDBO_OK;
+  for (const InstDev& I : c->insts_h)
+    HIPCHK(c, launch_frag_pack(I.Xs[c->parity], I.B, (int64_t)I.ld * element_bytes(c->prec),
+                               !dense_cfg(c->cfg).dma, I.Xf[c->parity], c->stream));
+  return PDBO_OK;
+}
+
+// One-wave tiles or cfg's, by the estimated time of a step (us).  A one-wave
+// tile is bound by its chain of K chunks (0.1 us each, FP32's MFMAs 0.125 us a
+// fragment), the launch by the operand bytes its waves take from the L2s (14.5
+// MB/us); a workgroup tile by its K chunks (0.34 us for 64x64, longer as it
+// grows).  Measured with the rest of the iteration (us, one-wave / tiles):
+// n = 200, B = 16 fp32 6.4 / 10.4; n = 2000, B = 16 fp32 15.7 / 41.6; n = 5000,
+// B = 16 int8 10.8 / 17.0; n = 3001, B = 100 bf16 17.0 / 20.8; n = 1000, B = 300
+// fp32 18.9 / 27.3; the tiles stay where restarts are many: n = 5000, B = 100
+// int8 22.4 / 20.8; n = 3000, B = 200 int8 20.2 / 16.9; n = 1000, B = 1024
+// int8 18.5 / 14.1.  Their copy of A is bounded at 512 MB.
+int frag_choice(const pdbo_ctx* c) {
+  const int EB = element_bytes(c->prec);
+  const TileCfgInfo& cf = dense_cfg(c->cfg);
+  const double size = (double)cf.BM * cf.BN / 4096.0;
+  const double chunk = c->prec == PDBO_FP32 ? 0.6 * size : 0.34 * std::sqrt(size);
+  double bytes = 0, tiles = 0;
+  int nk = 1;
+  for (const InstDev& I : c->insts_h) {
+    nk = std::max(nk, I.ld * EB / 128);
+    bytes += (double)I.n * I.ld * EB;
+    tiles += (double)((I.n + cf.BM - 1) / cf.BM) * ((I.B + cf.BN - 1) / cf.BN);
+  }
+  if (bytes > (double)(512 << 20)) return -1;
+  double best = 2.0 + nk * chunk * std::ceil(tiles / (256.0 * (size > 1 ? 1 : 3)));
+  int id = -1;
+  for (int f = 0; f < dense_num_frags(); ++f) {
+    const int fn = dense_frag_cfg(f).BN / 16;
+    double waves = 0, moved = 0;
+    for (const InstDev& I : c->insts_h) {
+      const double w = (double)((I.n + 15) / 16) * ((I.B + 16 * fn - 1) / (16 * fn));
+      waves += w;
+      moved += w * (I.ld * EB / 128) * (1 + fn) * 2048;
+    }
+    const double chain =
+        nk * (c->prec == PDBO_FP32 ? 0.125 * fn * std::ceil(waves / 1024) : 0.08 + 0.02 * fn);
+    const double us = 2.0 + std::max(chain, moved / 14.5e6);
+    if (us < best) {
+      best = us;
+      id = f;
+    }
+  }
+  return id;
+}
+
+pdbo_status setup_frags(pdbo_ctx* c) {
+  const int EB = element_bytes(c->prec), staged = !dense_cfg(c->cfg).dma;
+  const FragCfgInfo& fc = dense_frag_cfg(c->frag);
+  for (InstDev& I : c->insts_h) {
+    const int64_t rb = (int64_t)I.ld * EB;
+    uint8_t* Af = nullptr;
+    STCHK(dalloc(c, &Af, (size_t)roundup(I.n, 16) * rb));
+    HIPCHK(c, launch_frag_pack(I.A, I.n, rb, staged, Af, c->stream));
+    I.Af = Af;
+    for (int p = 0; p < 2; ++p) STCHK(dalloc(c, &I.Xf[p], (size_t)roundup(I.B, 16) * rb));
+  }
+  tile_table(c->insts_h, fc.BM, fc.BN, c->frag_tiles_h, c->frag_off, c->frag_cnt);
+  STCHK(dalloc(c, &c->frag_tiles_d, c->frag_tiles_h.size()));
+  HIPCHK(c, hipMemcpyAsync(c->frag_tiles_d, c->frag_tiles_h.data(),
+                           c->frag_tiles_h.size() * sizeof(TileDev), hipMemcpyHostToDevice, c->stream));
+  return frag_shadow(c);
 }
 
 pdbo_status upload_dense_tables(pdbo_ctx* c) {
@@ -1223,6 +1330,16 @@ hipError_t launch_eval_gemm(const pdbo_ctx* c, const TileDev* tiles, int ntiles,
   return hipSuccess;
 }
 
+// One step over tiles t0 .. t0 + nt - 1 of the context's tile table, or f0 ..
+// f0 + nf - 1 of its one-wave tiles.
+hipError_t launch_dense_step(const pdbo_ctx* c, int t0, int nt, int f0, int nf, int am0, int amn) {
+  if (c->frag >= 0)
+    return launch_dense_frag(c->frag, c->prec, c->par.g_kind, c->frag_tiles_d + f0, nf, c->insts_d,
+                             c->parity, !dense_cfg(c->cfg).dma, c->stream, am0, amn);
+  return launch_dense_gemm(c->cfg, c->prec, EPI_STEP, c->par.g_kind, c->tiles_d + t0, nt, c->insts_d,
+                           c->parity, 0, c->stream, am0, amn);
+}
+
 pdbo_status dense_one_step(pdbo_ctx* c) {
   const bool do_eval = ((c->t_host + 1) % c->eval_every) == 0;
   const int ninst = (int)c->insts_h.size();
@@ -1233,8 +1350,7 @@ pdbo_status dense_one_step(pdbo_ctx* c) {
     HIPCHK(c, launch_dual_scalar(c->insts_d, ninst, c->B, c->par.g_kind, c->parity, c->stream));
   if (c->grouped) {
     t_begin(c, tl, PDBO_K_STEP);
-    HIPCHK(c, launch_dense_gemm(c->cfg, c->prec, EPI_STEP, c->par.g_kind, c->tiles_d,
-                                (int)c->tiles_h.size(), c->insts_d, c->parity, 0, c->stream, 0,
+    HIPCHK(c, launch_dense_step(c, 0, (int)c->tiles_h.size(), 0, (int)c->frag_tiles_h.size(), 0,
                                 c->argmin_pending ? ninst : 0));
     t_end(c, tl);
     if (do_eval) {
@@ -1260,9 +1376,9 @@ pdbo_status dense_one_step(pdbo_ctx* c) {
   } else {
     for (int k = 0; k < ninst; ++k) {
       t_begin(c, tl, PDBO_K_STEP);
-      HIPCHK(c, launch_dense_gemm(c->cfg, c->prec, EPI_STEP, c->par.g_kind,
-                                  c->tiles_d + c->tile_off[k], c->tile_cnt[k], c->insts_d,
-                                  c->parity, 0, c->stream, k, c->argmin_pending ? 1 : 0));
+      const bool fr = c->frag >= 0;
+      HIPCHK(c, launch_dense_step(c, c->tile_off[k], c->tile_cnt[k], fr ? c->frag_off[k] : 0,
+                                  fr ? c->frag_cnt[k] : 0, k, c->argmin_pending ? 1 : 0));
       t_end(c, tl);
     }
     if (do_eval)
@@ -1592,7 +1708,8 @@ const char* pdbo_last_global_error(void) { return g_last_error.c_str(); }
 
 const char* pdbo_tile_name(const pdbo_ctx* ctx) {
   if (!ctx) return "";
-  if (ctx->kind == 0) return dense_cfg(ctx->cfg).name;
+  if (ctx->kind == 0)
+    return ctx->frag >= 0 ? dense_frag_cfg(ctx->frag).name : dense_cfg(ctx->cfg).name;
   if (ctx->kind == 1) return csr_variant_name(ctx->csr, ctx->compact);
   if (ctx->kind == 3) return "csr_rows";
   return "";
@@ -1651,6 +1768,12 @@ static pdbo_status dense_init(int k, const pdbo_qubo* probs, const pdbo_params* 
     for (const InstDev& I : c->insts_h) work += (double)I.n * I.n * I.B;
     const bool want = e ? std::atoi(e) != 0 : work >= (double)(1 << 30);
     if (want) st = autotune_dense(c);
+  }
+  if (st == PDBO_OK && pars[0].tile == 0) {
+    // PDBO_FRAG=0 keeps the tiles, 1 .. dense_num_frags() takes that width
+    const char* e = std::getenv("PDBO_FRAG");
+    c->frag = e && *e ? std::min(std::atoi(e), dense_num_frags()) - 1 : frag_choice(c);
+    if (c->frag >= 0) st = setup_frags(c);
   }
   if (st == PDBO_OK) st = upload_dense_tables(c);
   if (st != PDBO_OK) {
@@ -2509,6 +2632,7 @@ pdbo_status qubo_gda_set_state(pdbo_ctx* c, const float* x, const float* y, int6
   if (c->kind == 0 && c->prec != PDBO_FP32) Xs = c->insts_h[0].Xs[c->parity];
   HIPCHK(c, launch_set_state((const float*)tx.p, (const float*)ty.p, c->B, n, ld, X, Y, Xs, c->prec,
                              c->stream));
+  if (c->kind == 0 && x) STCHK(frag_shadow(c));  // without x the shadow stands
   c->t_host = t;
   c->full_until = t + full_eval_iters();
   if (c->kind == 0 && y && c->insts_h[0].ys) {
@@ -2579,6 +2703,7 @@ pdbo_status qubo_gda_restart(pdbo_ctx* c, const double* x0) {
     HIPCHK(c, launch_init_state((const double*)t.p, B, n, I.ld, y0, I.X[0], I.Y,
                                 c->prec == PDBO_FP32 ? nullptr : I.Xs[0], c->prec, I.Xr, c->par.seed,
                                 c->stream));
+    STCHK(frag_shadow(c));
     const int64_t zero = 0;
     HIPCHK(c, hipMemcpyAsync(I.t_dev, &zero, sizeof(zero), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(I.inc, &init, sizeof(init), hipMemcpyHostToDevice, c->stream));
@@ -2901,6 +3026,14 @@ pdbo_status qubo_dual_bound(pdbo_ctx* c, double ybar, int32_t iters, double* low
     STCHK(dalloc(c, &c->cert_x, 2 * (size_t)ld));
     STCHK(dalloc(c, &c->cert_y, (size_t)ld));
     STCHK(dalloc(c, &c->cert_xs, 2 * (size_t)ld * 4));
+    if (c->kind == 0 && c->frag >= 0) {
+      STCHK(dalloc(c, &c->cert_xf, 2 * 16 * (size_t)ld * element_bytes(c->prec)));
+      STCHK(dalloc(c, &c->cert_tiles, (size_t)(n + 15) / 16));
+      std::vector<TileDev> tiles;
+      for (int m = 0; m < (n + 15) / 16; ++m) tiles.push_back(TileDev{0, 16 * m, 0, m});
+      HIPCHK(c, hipMemcpy(c->cert_tiles, tiles.data(), tiles.size() * sizeof(TileDev),
+                          hipMemcpyHostToDevice));
+    }
     STCHK(dalloc(c, &c->cert_xr, (size_t)ld));
     STCHK(dalloc(c, &c->cert_rows, 4 * (size_t)n));
     STCHK(dalloc(c, &c->cert_res, 4));
@@ -2932,13 +3065,23 @@ pdbo_status qubo_dual_bound(pdbo_ctx* c, double ybar, int32_t iters, double* low
     I.ys = nullptr;
     I.gp.beta = 0.f;
     I.gp.gkind = PDBO_G_QUAD;
+    const int EB = element_bytes(c->prec);
+    I.Xf[0] = c->cert_xf;
+    I.Xf[1] = c->cert_xf ? c->cert_xf + 16 * (size_t)ld * EB : nullptr;
     if (c->prec != PDBO_FP32)
       HIPCHK(c, launch_set_state(x0, nullptr, 1, n, ld, x0, nullptr, I.Xs[0], c->prec, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->scratch_inst_d, &I, sizeof(I), hipMemcpyHostToDevice, c->stream));
     int parity = 0;
+    const bool fr = c->frag >= 0;  // then by one-wave tiles, as the context's steps
+    const int staged = !dense_cfg(c->cfg).dma;
+    if (fr) HIPCHK(c, launch_frag_pack(I.Xs[0], 1, (int64_t)ld * EB, staged, I.Xf[0], c->stream));
     for (int t = 0; t < iters; ++t) {
-      HIPCHK(c, launch_dense_gemm(c->cfg, c->prec, EPI_STEP, PDBO_G_QUAD, c->tiles_d,
-                                  (int)c->tiles_h.size(), c->scratch_inst_d, parity, 0, c->stream));
+      if (fr)
+        HIPCHK(c, launch_dense_frag(0, c->prec, PDBO_G_QUAD, c->cert_tiles, (n + 15) / 16,
+                                    c->scratch_inst_d, parity, staged, c->stream, 0, 0));
+      else
+        HIPCHK(c, launch_dense_gemm(c->cfg, c->prec, EPI_STEP, PDBO_G_QUAD, c->tiles_d,
+                                    (int)c->tiles_h.size(), c->scratch_inst_d, parity, 0, c->stream));
       parity ^= 1;
     }
     xhat = I.X[parity];

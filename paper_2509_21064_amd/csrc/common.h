@@ -58,6 +58,8 @@ struct InstDev {
   float* X[2];
   float* Y;
   uint8_t* Xs[2];         // shadows; for FP32 these alias X
+  const uint8_t* Af;      // dense_frag: A and the shadow in fragment order (nullptr: not used);
+  uint8_t* Xf[2];         //   a step then writes Xf and leaves Xs (but not FP32's X) as it was
   int8_t* Xr;
   float* G;               // gradient output of the GRAD epilogue
   int64_t* Sacc;          // [B] x_r^T Ahat x_r, accumulated by integer atomics
@@ -279,6 +281,23 @@ struct TileCfgInfo {
 };
 int dense_num_cfgs();
 const TileCfgInfo& dense_cfg(int id);
+
+// dense_frag (dense.hip): tiles of fm x fn MFMA fragments, one wave each, by id.
+// staged: 1 for the K order of the register-staged tiles, 0 for that of the
+// direct-to-LDS tiles.
+struct FragCfgInfo {
+  const char* name;
+  int BM, BN;
+};
+int dense_num_frags();
+const FragCfgInfo& dense_frag_cfg(int id);
+hipError_t launch_dense_frag(int id, int prec, int gkind, const TileDev* tiles, int ntiles,
+                             const InstDev* insts, int parity, int staged, hipStream_t s, int am0,
+                             int amn);
+// rows of `rbytes` bytes (a multiple of 128) in fragment order: groups of 16
+// rows (the last one filled up with zero rows), K chunk by K chunk
+hipError_t launch_frag_pack(const uint8_t* src, int rows, int64_t rbytes, int staged, uint8_t* dst,
+                            hipStream_t s);
 
 // gkind: the kind of g (GdaP::gkind) of every instance of the launch; only the
 // step epilogue uses it.  parity: the operand shadow the step and gradient

@@ -333,15 +333,27 @@ __device__ __forceinline__ void best_of_B_extra(const InstDev& I) {
   best_of_B<NT>(I, 1, threadIdx.x, sF, sb, &improved);
 }
 
+// Fragment order: byte `o` of row r (rows of rbytes bytes) when the 16-byte
+// pieces the 64 lanes of an MFMA operand hold (row lane % 16; chunk lane / 16 of
+// each half of a 128-byte K chunk) are stored one lane after the other.  The
+// halves are chunks q and q + 4 (direct-to-LDS tiles), or 2q and 2q + 1 (staged).
+__device__ __forceinline__ size_t frag_offset(int r, int o, int rbytes, int staged) {
+  const int c = (o >> 4) & 7;
+  const int q = staged ? c >> 1 : c & 3, h = staged ? c & 1 : c >> 2;
+  return ((((size_t)(r >> 4) * (rbytes >> 7) + (o >> 7)) * 2 + h) << 10) +
+         ((q * 16 + (r & 15)) << 4) + (o & 15);
+}
+
 // Epilogue of one tile, shared by both main loops.  STEP/GRAD: lane holds
 // rows ibase+16*fm+r (r = 0..3) of restart column bbase+16*fn.  GK is the kind
 // of g (0 quadratic, 1 entropy) as a constant: with the kind read at run time
 // the compiler evaluates both forms of g and g' for every element, and the
 // entropy's logarithms alone cost more than the rest of the update.
-template <int BM, int BN, int WM, int WN, int P, int EPI, int GK = 0>
+// FRAG: the shadow goes to Xf in fragment order (staged: whose K order).
+template <int BM, int BN, int WM, int WN, int P, int EPI, int GK = 0, bool FRAG = false>
 __device__ __forceinline__ void gemm_epilogue(
     typename PT<P>::Acc (&acc)[BM / WM / 16][BN / WN / 16], const TileDev& td, const InstDev& I,
-    int parity, int lane, int wm, int wn) {
+    int parity, int lane, int wm, int wn, int staged = 0) {
   constexpr int WTM = BM / WM, WTN = BN / WN;
   constexpr int FM = WTM / 16, FN = WTN / 16;
   const int n = I.n, ld = I.ld, B = I.B;
@@ -429,15 +441,20 @@ __device__ __forceinline__ void gemm_epilogue(
                               ((uint32_t)(xo[3] > 0.5f) << 24);
           *gptr((uint32_t*)(I.Xr + off)) = xr;
           if (I.nflip) record_flips(I, b, i, n, r.xro[fn], xr);
+          uint8_t* sh = Xsn + off * PT<P>::EB;
+          if constexpr (FRAG)
+            sh = I.Xf[parity ^ 1] + frag_offset(b, i * PT<P>::EB, ld * PT<P>::EB, staged);
           if constexpr (P == P_BF16) {
             u32x2 v;
             v.x = (uint32_t)f32_to_bf16_rne(xo[0]) | ((uint32_t)f32_to_bf16_rne(xo[1]) << 16);
             v.y = (uint32_t)f32_to_bf16_rne(xo[2]) | ((uint32_t)f32_to_bf16_rne(xo[3]) << 16);
-            *gptr((u32x2*)(Xsn + off * 2)) = v;
+            *gptr((u32x2*)sh) = v;
           } else if constexpr (P == P_FP8) {
-            *gptr((uint32_t*)(Xsn + off)) = pack_fp8x4(xo[0], xo[1], xo[2], xo[3]);
+            *gptr((uint32_t*)sh) = pack_fp8x4(xo[0], xo[1], xo[2], xo[3]);
           } else if constexpr (P == P_I8) {
-            *gptr((uint32_t*)(Xsn + off)) = pack_q8x4(xo[0], xo[1], xo[2], xo[3]);
+            *gptr((uint32_t*)sh) = pack_q8x4(xo[0], xo[1], xo[2], xo[3]);
+          } else if constexpr (FRAG) {
+            *gptr((f32x4*)sh) = xo;
           }
         }
       }
@@ -1017,6 +1034,77 @@ __global__ void __launch_bounds__(64 * WM * WN)
   __builtin_amdgcn_s_waitcnt(0);  // no DMA into LDS may outlive the workgroup
 }
 
+// ------------------------------------------------------------ one wave a tile
+//
+// For shapes with too few tiles to fill the chip: a workgroup is one wave with a
+// tile of FM x FN fragments.  Both operands are stored in fragment order, so a
+// load is 1 KB of consecutive bytes straight into the fragment registers, U K
+// chunks ahead, with no LDS and no barrier.  (From row-major operands the same
+// loads touch 16 rows with 16 bytes a lane and take about 100 cycles each.)
+template <int FN, int U, int P, int GK>
+__global__ void __launch_bounds__(64)
+    dense_frag(const TileDev* __restrict__ tiles, int ntiles, const InstDev* __restrict__ insts,
+               int parity, int am0, int staged) {
+  if (blockIdx.x >= ntiles) {
+    best_of_B_extra<64>(insts[am0 + blockIdx.x - ntiles]);
+    return;
+  }
+  using Acc = typename PT<P>::Acc;
+  const int lane = threadIdx.x;
+  const TileDev td = tiles[blockIdx.x];
+  const InstDev& I = insts[td.inst];
+  const int nk = I.ld * PT<P>::EB / 128;
+  // groups of 16 restarts past the end repeat the last one (nothing of them is stored)
+  const int gb = (I.B + 15) / 16 - 1;
+  const uint8_t* pa = I.Af + (size_t)(td.m0 / 16) * nk * 2048 + lane * 16;
+  const uint8_t* pb[FN];
+#pragma unroll
+  for (int j = 0; j < FN; ++j)
+    pb[j] = I.Xf[parity] + (size_t)min(td.n0 / 16 + j, gb) * nk * 2048 + lane * 16;
+
+  Acc acc[1][FN];
+#pragma unroll
+  for (int j = 0; j < FN; ++j) acc[0][j] = Acc{0, 0, 0, 0};
+  u32x4 ra[U][2], rb[U][FN][2];
+  auto load = [&](int u, int k) {
+    const size_t o = (size_t)k * 2048;
+    ra[u][0] = *gptr((const u32x4*)(pa + o));
+    ra[u][1] = *gptr((const u32x4*)(pa + o + 1024));
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      rb[u][j][0] = *gptr((const u32x4*)(pb[j] + o));
+      rb[u][j][1] = *gptr((const u32x4*)(pb[j] + o + 1024));
+    }
+  };
+  auto mm = [&](int u) {
+#pragma unroll
+    for (int j = 0; j < FN; ++j) mfma_chunk<P>(acc[0][j], ra[u], rb[u][j]);
+  };
+#pragma unroll
+  for (int u = 0; u < U; ++u) load(u, min(u, nk - 1));
+  int kc = 0;
+  for (; kc + 2 * U <= nk; kc += U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      mm(u);
+      load(u, kc + U + u);
+      __builtin_amdgcn_sched_barrier(0);  // keep the loads U chunks ahead
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (kc + u < nk) mm(u);
+    if (kc + U + u < nk) load(u, kc + U + u);
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (kc + U + u < nk) mm(u);
+  gemm_epilogue<16, 16 * FN, 1, 1, P, EPI_STEP, GK, true>(acc, td, I, parity, lane, 0, 0, staged);
+}
+
+// id, fragments along the restarts, K chunks in flight
+#define PDBO_FRAG_CFGS(X) X(0, 1, 8) X(1, 2, 8)
+
 // ---------------------------------------------------------------- tile table
 
 // id, block tile BM x BN, waves WM x WN, main loop (0: register-staged double
@@ -1067,14 +1155,23 @@ hipError_t launch_step_g1(int cfg, int prec, const TileDev* tiles, int ntiles, c
                           int parity, int grid, hipStream_t s, int am0, int amn);
 hipError_t launch_step_g2(int cfg, int prec, const TileDev* tiles, int ntiles, const InstDev* insts,
                           int parity, int grid, hipStream_t s, int am0, int amn);
+hipError_t launch_frag_g0(int id, int prec, const TileDev* tiles, int ntiles, const InstDev* insts,
+                          int parity, int staged, hipStream_t s, int am0, int amn);
+hipError_t launch_frag_g1(int id, int prec, const TileDev* tiles, int ntiles, const InstDev* insts,
+                          int parity, int staged, hipStream_t s, int am0, int amn);
+hipError_t launch_frag_g2(int id, int prec, const TileDev* tiles, int ntiles, const InstDev* insts,
+                          int parity, int staged, hipStream_t s, int am0, int amn);
 
 #if PDBO_DENSE_PART >= 1
 #if PDBO_DENSE_PART == 1
 #define PDBO_STEP_FN launch_step_g0
+#define PDBO_FRAG_FN launch_frag_g0
 #elif PDBO_DENSE_PART == 2
 #define PDBO_STEP_FN launch_step_g1
+#define PDBO_FRAG_FN launch_frag_g1
 #else
 #define PDBO_STEP_FN launch_step_g2
+#define PDBO_FRAG_FN launch_frag_g2
 #endif
 // The kind of g of this part's step kernels is a compile-time constant: read at
 // run time it made the compiler evaluate every form of g and g' for each
@@ -1106,6 +1203,35 @@ hipError_t PDBO_STEP_FN(int cfg, int prec, const TileDev* tiles, int ntiles, con
     default:
       return hipErrorInvalidValue;
   }
+}
+template <int P, int GK>
+static hipError_t launch_frag(int id, const TileDev* tiles, int ntiles, const InstDev* insts,
+                              int parity, int staged, hipStream_t s, int am0, int amn) {
+  switch (id) {
+#define X(id, fn, u)                                                                            \
+  case id:                                                                                      \
+    hipLaunchKernelGGL((dense_frag<fn, u, P, GK>), dim3(ntiles + amn), dim3(64), 0, s,          \
+                       tiles, ntiles, insts, parity, am0, staged);                              \
+    return hipGetLastError();
+    PDBO_FRAG_CFGS(X)
+#undef X
+    default:
+      return hipErrorInvalidValue;
+  }
+}
+
+hipError_t PDBO_FRAG_FN(int id, int prec, const TileDev* tiles, int ntiles, const InstDev* insts,
+                        int parity, int staged, hipStream_t s, int am0, int amn) {
+  constexpr int GK = PDBO_DENSE_PART - 1;
+#define PDBO_L(P) launch_frag<P, GK>(id, tiles, ntiles, insts, parity, staged, s, am0, amn)
+  switch (prec) {
+    case P_F32: return PDBO_L(P_F32);
+    case P_BF16: return PDBO_L(P_BF16);
+    case P_FP8: return PDBO_L(P_FP8);
+    case P_I8: return PDBO_L(P_I8);
+    default: return hipErrorInvalidValue;
+  }
+#undef PDBO_L
 }
 #endif  // PDBO_DENSE_PART >= 1
 
@@ -1157,6 +1283,51 @@ hipError_t launch_dense_gemm(int cfg, int prec, int epi, int gkind, const TileDe
     default:
       return hipErrorInvalidValue;
   }
+}
+
+static const FragCfgInfo kFrags[] = {
+#define X(id, fn, u) {"frag_16x16x" #fn, 16, 16 * fn},
+    PDBO_FRAG_CFGS(X)
+#undef X
+};
+int dense_num_frags() { return (int)(sizeof(kFrags) / sizeof(kFrags[0])); }
+const FragCfgInfo& dense_frag_cfg(int id) { return kFrags[id]; }
+
+hipError_t launch_dense_frag(int id, int prec, int gkind, const TileDev* tiles, int ntiles,
+                             const InstDev* insts, int parity, int staged, hipStream_t s, int am0,
+                             int amn) {
+  switch (gkind) {
+    case 0: return launch_frag_g0(id, prec, tiles, ntiles, insts, parity, staged, s, am0, amn);
+    case 1: return launch_frag_g1(id, prec, tiles, ntiles, insts, parity, staged, s, am0, amn);
+    case 2: return launch_frag_g2(id, prec, tiles, ntiles, insts, parity, staged, s, am0, amn);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// one wave per (group of 16 rows, K chunk), a lane per 16-byte piece of each half
+__global__ void __launch_bounds__(256)
+    frag_pack_kernel(const uint8_t* __restrict__ src, int rows, int64_t rbytes, int staged,
+                     int64_t units, uint8_t* __restrict__ dst) {
+  const int64_t u = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (u >= units) return;
+  const int lane = threadIdx.x & 63, q = lane >> 4;
+  const int64_t nk = rbytes / 128, k = u % nk, r = u / nk * 16 + (lane & 15);
+  const uint8_t* row = src + r * rbytes + k * 128;
+  u32x4 v0 = {0, 0, 0, 0}, v1 = {0, 0, 0, 0};
+  if (r < rows) {
+    v0 = *(const u32x4*)(row + (staged ? 2 * q : q) * 16);
+    v1 = *(const u32x4*)(row + (staged ? 2 * q + 1 : q + 4) * 16);
+  }
+  *(u32x4*)(dst + u * 2048 + lane * 16) = v0;
+  *(u32x4*)(dst + u * 2048 + 1024 + lane * 16) = v1;
+}
+
+hipError_t launch_frag_pack(const uint8_t* src, int rows, int64_t rbytes, int staged, uint8_t* dst,
+                            hipStream_t s) {
+  const int64_t units = (int64_t)((rows + 15) / 16) * (rbytes / 128);
+  hipLaunchKernelGGL(frag_pack_kernel, dim3((unsigned)((units + 3) / 4)), dim3(256), 0, s, src,
+                     rows, rbytes, staged, units, dst);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- best of B
