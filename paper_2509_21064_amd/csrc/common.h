@@ -613,4 +613,10 @@ hipError_t launch_sat_fwd(const SatDev& d, const float* x, const float* y, int n
 hipError_t launch_sat_bwd(const SatDev& d, const float* x, const float* y, const float* dL,
                           int nb, float* dx, float* dy, hipStream_t s);
 
+// Dynamic LDS above the 64 KB every kernel may take has to be asked for.
+inline hipError_t allow_lds(const void* kern, size_t bytes) {
+  if (bytes <= 65536) return hipSuccess;
+  return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
 }  // namespace pdbo

@@ -329,8 +329,7 @@ static hipError_t launch_kr(const KcutDev& d, int nsteps, hipStream_t s) {
   auto kern = d.gp.gkind == 0 ? kcut_resident<K, 0> : kcut_resident<K, 1>;
   const int nc = kcutres_copies(d.n, K), np = kr_rows32(d.n);
   const size_t lds = (size_t)nc * np * kr_stride(K) * 4 + np + kKrSmall;
-  hipError_t e =
-      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipError_t e = allow_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(d.B), dim3(kKrThreads), lds, s, d, nsteps, nc);
   return hipGetLastError();

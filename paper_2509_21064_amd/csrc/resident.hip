@@ -445,8 +445,7 @@ template <int R, bool SEQ, int GK, bool LDSE>
 static hipError_t launch_res_k(const CsrDev& d, int64_t t0, int nsteps, hipStream_t s) {
   auto kern = csr_resident<R, SEQ, GK, LDSE>;
   const size_t lds = csr_resident_lds(d.n, d.nrent, LDSE);
-  hipError_t e =
-      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipError_t e = allow_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(d.B), dim3(kResThreads), lds, s, d, t0, nsteps);
   return hipGetLastError();

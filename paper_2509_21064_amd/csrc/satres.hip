@@ -419,8 +419,7 @@ static hipError_t launch_sr_k(const SatDev& d, int64_t t0, int nsteps, hipStream
   auto kern = sat_resident<K, R, GK>;
   const int words = sr_words(d.n), nc = satres_copies(d.n, K);
   const size_t lds = (size_t)nc * words * 4 + kSrSmall;
-  hipError_t e =
-      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipError_t e = allow_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(d.B), dim3(kSrThreads), lds, s, d, t0, nsteps, words, nc);
   return hipGetLastError();
@@ -513,8 +512,7 @@ static hipError_t launch_sra_k(const SatDev& d, const float* X, int ldx, const f
   const int r = (d.n + kSrThreads - 1) / kSrThreads;
   auto kern = r <= 4 ? sat_adjoint_res<K, 4, MODE, GK>
                      : r <= 8 ? sat_adjoint_res<K, 8, MODE, GK> : sat_adjoint_res<K, 20, MODE, GK>;
-  hipError_t e =
-      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipError_t e = allow_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(nb), dim3(kSrThreads), lds, s, d, X, ldx, Y, dL, dx, dy, ldo, words, nc);
   return hipGetLastError();
@@ -606,8 +604,7 @@ static hipError_t launch_srf(const SatDev& d, const float* x, const float* y, in
                              hipStream_t s) {
   const size_t lds = (size_t)sr_words(d.n) * 4;
   auto kern = d.gp.gkind == 0 ? sat_fwd_res<K, 0> : sat_fwd_res<K, 1>;
-  hipError_t e =
-      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipError_t e = allow_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(nb), dim3(kSrThreads), lds, s, d, x, y, L);
   return hipGetLastError();
