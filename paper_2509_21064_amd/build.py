@@ -45,6 +45,7 @@ UNITS = [
     ("spmm.hip", "spmm.o", []),
     ("cert.hip", "cert.o", []),
     ("kcut.hip", "kcut.o", []),
+    ("rowsplit.hip", "rowsplit.o", []),
     ("kcutres.hip", "kcutres.o", []),
     ("realw.hip", "realw.o", []),
     ("api.hip", "api.o", []),

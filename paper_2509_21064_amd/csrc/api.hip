@@ -1670,6 +1670,108 @@ void res_layout(int n, const int32_t* rp, const int32_t* col, const int32_t* val
   }
 }
 
+// rowsplit.hip's layout (SpmmDev::sent): segments of `rows` rows, each with its
+// rows ordered by their groups of entries per range.
+struct SplitLayout {
+  std::vector<uint32_t> ent;
+  std::vector<int2> meta;
+  std::vector<int32_t> row;
+  int segs = 0, rows = 0, range = 0, ranges = 0;
+};
+
+constexpr int kSplitRange = 40000;  // columns of x in LDS at a time (160 KB)
+
+void split_layout(const CsrCanon& C, int nseg, SplitLayout& L) {
+  const int n = C.n;
+  L.rows = roundup((n + nseg - 1) / nseg, 64);
+  L.segs = (n + L.rows - 1) / L.rows;
+  L.ranges = (n + kSplitRange - 1) / kSplitRange;
+  L.range = roundup((n + L.ranges - 1) / L.ranges, 4);
+  const int H = L.ranges;
+  // first entry of each row in each range (columns increase along a row)
+  std::vector<int32_t> at((size_t)n * (H + 1));
+  for (int i = 0; i < n; ++i) {
+    int p = C.rp[i];
+    for (int h = 0; h < H; ++h) {
+      at[(size_t)i * (H + 1) + h] = p;
+      while (p < C.rp[i + 1] && C.col[p] < (h + 1) * L.range) ++p;
+    }
+    at[(size_t)i * (H + 1) + H] = C.rp[i + 1];
+  }
+  auto groups = [&](int i, int h) {
+    const int32_t* a = &at[(size_t)i * (H + 1) + h];
+    return (a[1] - a[0] + 3) / 4;
+  };
+  const int sps = L.rows / 64;
+  L.row.assign((size_t)L.segs * L.rows, -1);
+  L.meta.resize((size_t)L.segs * sps * H);
+  int64_t tot = 0;
+  for (int g = 0; g < L.segs; ++g) {
+    const int row0 = g * L.rows, cnt = std::min(L.rows, n - row0);
+    int32_t* row = &L.row[row0];
+    for (int q = 0; q < cnt; ++q) row[q] = q;
+    std::stable_sort(row, row + cnt, [&](int32_t a, int32_t b) {
+      for (int h = 0; h < H; ++h)
+        if (const int d = groups(row0 + a, h) - groups(row0 + b, h)) return d > 0;
+      return false;
+    });
+    for (int s = 0; s < sps; ++s)
+      for (int h = 0; h < H; ++h) {
+        int ng = 0;
+        for (int q = s * 64; q < std::min(cnt, s * 64 + 64); ++q)
+          ng = std::max(ng, groups(row0 + row[q], h));
+        L.meta[((size_t)g * sps + s) * H + h] = make_int2((int)tot, ng);
+        tot += ng;
+      }
+  }
+  L.ent.assign((size_t)(tot + 8) * 256, 0u);  // the kernel reads ahead
+  for (size_t q = 0; q < L.row.size(); ++q) {
+    if (L.row[q] < 0) continue;
+    const int i = (int)(q / L.rows) * L.rows + L.row[q];
+    for (int h = 0; h < H; ++h) {
+      const int32_t* a = &at[(size_t)i * (H + 1) + h];
+      uint32_t* to = &L.ent[(size_t)L.meta[q / 64 * H + h].x * 256 + 4 * (q % 64)];
+      for (int p = a[0], k = 0; p < a[1]; ++p, ++k) {
+        const _Float16 w = (_Float16)(float)C.val[p];
+        uint16_t wb;
+        std::memcpy(&wb, &w, 2);
+        to[(size_t)(k / 4) * 256 + k % 4] = (uint32_t)(C.col[p] - h * L.range) | ((uint32_t)wb << 16);
+      }
+    }
+  }
+}
+
+// Row segments per restart of rowsplit.hip, or 0 for the row-parallel kernel
+// (PDBO_CSR_SPLIT: 0 never, 1 wherever it can).  Estimated iterations, fitted to
+// (us, segments / row-parallel): n = 5 * 10^4: d = 100 B = 10 27 / 53, B = 48
+// 99 / 165; d = 20, B = 10 19.4 / 22.4; d = 3, B = 10 18.7 / 16.3; n = 10^4,
+// B = 10: d = 100 16.8 / 18.2, d = 5 12.3 / 10.5.  A segment holds at most eight
+// slices of 64 rows a wave; the weights are exact in float16 and a row's
+// rounded sum in float32.
+int split_choice(const CsrCanon& C, int B) {
+  const char* e = std::getenv("PDBO_CSR_SPLIT");
+  if (e && std::atoi(e) == 0) return 0;
+  const int n = C.n, ns = (n + 63) / 64;
+  const double nnz = (double)C.col.size();
+  if (B > 64 || C.amax > 2048 || C.rowabs >= (1 << 24) || n > 65536 || nnz * 1.5 + 256.0 * ns > 2e9)
+    return 0;
+  double best = 1e300;
+  int nseg = 0;
+  for (int k = 1; k <= 256 && (k == 1 || (k - 1) * 16 < ns); ++k) {
+    const int rows = roundup((n + k - 1) / k, 64);
+    if (rows > 8 * 1024) continue;
+    int longest = 0;
+    for (int i = 0; i < n; i += rows) longest = std::max(longest, C.rp[std::min(n, i + rows)] - C.rp[i]);
+    const double us = 9.0 + std::ceil(B * k / 256.0) * (2.5 + 1.3e-4 * n + 4.5e-5 * (longest + 2.0 * rows));
+    if (us < best) {
+      best = us;
+      nseg = k;
+    }
+  }
+  const double rows = 9.0 + 0.1 * B + 6e-6 * (double)n * B + nnz * (1.5e-6 + 6e-7 * B);
+  return nseg && ((e && std::atoi(e) == 1) || best < rows) ? nseg : 0;
+}
+
 // resident.hip's: byte offsets, c' by position, slices up to the compiled size
 void csr_res_layout(const CsrCanon& C, const std::vector<int32_t>& order, ResLayout& L) {
   const int n = C.n, np = csr_resident_rows(n) * 1024, nc = csr_resident_copies(n);
@@ -1711,7 +1813,7 @@ const char* pdbo_tile_name(const pdbo_ctx* ctx) {
   if (ctx->kind == 0)
     return ctx->frag >= 0 ? dense_frag_cfg(ctx->frag).name : dense_cfg(ctx->cfg).name;
   if (ctx->kind == 1) return csr_variant_name(ctx->csr, ctx->compact);
-  if (ctx->kind == 3) return "csr_rows";
+  if (ctx->kind == 3) return ctx->spmm.sent ? "csr_split" : "csr_rows";
   return "";
 }
 
@@ -2038,6 +2140,28 @@ static pdbo_status spmm_init(const CsrCanon* C, const RealCanon* R, const pdbo_p
     const int nrb = (n + rows_per_wg - 1) / rows_per_wg;
     const int gpw = std::max(1, std::min(nrb, std::max(1, rowpar_grid_cap() / d.nslices)));
     d.grid = gpw * d.nslices;
+    SplitLayout split;  // host staging, alive until init syncs
+    // the segments' layout and restart-major state, or node-major row-parallel
+    if (const int nseg = C ? split_choice(*C, B) : 0) {
+      split_layout(*C, nseg, split);
+      d.grid = split.segs;
+      uint32_t* ent = nullptr;
+      int2* meta = nullptr;
+      int32_t* row = nullptr;
+      STCHK(dalloc(c, &ent, split.ent.size()));
+      STCHK(dalloc(c, &meta, split.meta.size()));
+      STCHK(dalloc(c, &row, split.row.size()));
+      HIPCHK(c, hipMemcpyAsync(ent, split.ent.data(), split.ent.size() * 4, hipMemcpyHostToDevice, c->stream));
+      HIPCHK(c, hipMemcpyAsync(meta, split.meta.data(), split.meta.size() * sizeof(int2),
+                               hipMemcpyHostToDevice, c->stream));
+      HIPCHK(c, hipMemcpyAsync(row, split.row.data(), split.row.size() * 4, hipMemcpyHostToDevice, c->stream));
+      d.sent = ent;
+      d.smeta = meta;
+      d.srow = row;
+      d.srows = split.rows;
+      d.srange = split.range;
+      d.sranges = split.ranges;
+    }
     int32_t *rp = nullptr, *col = nullptr;
     float* cps = nullptr;
     STCHK(dalloc(c, &rp, n + 1));
@@ -2494,9 +2618,14 @@ static void state_ptrs(pdbo_ctx* c, float** X, float** Y, int* ld, int* n) {
   }
 }
 
-// Row-parallel CSR: node-major device arrays <-> restart-major host arrays.
-static pdbo_status spmm_download(pdbo_ctx* c, const float* src, float* dst) {
+// Row-parallel CSR: node-major (rowsplit.hip: restart-major) device arrays <->
+// restart-major host arrays.
+static pdbo_status spmm_download(pdbo_ctx* c, const float* src, float* dst, bool node_major) {
   const int n = c->spmm.n, B = c->B;
+  if (!node_major) {
+    HIPCHK(c, hipMemcpy(dst, src, (size_t)n * B * sizeof(float), hipMemcpyDeviceToHost));
+    return PDBO_OK;
+  }
   std::vector<float> h((size_t)n * B);
   HIPCHK(c, hipMemcpy(h.data(), src, h.size() * sizeof(float), hipMemcpyDeviceToHost));
   for (int i = 0; i < n; ++i)
@@ -2504,8 +2633,12 @@ static pdbo_status spmm_download(pdbo_ctx* c, const float* src, float* dst) {
   return PDBO_OK;
 }
 
-static pdbo_status spmm_upload(pdbo_ctx* c, const float* src, float* dst) {
+static pdbo_status spmm_upload(pdbo_ctx* c, const float* src, float* dst, bool node_major) {
   const int n = c->spmm.n, B = c->B;
+  if (!node_major) {
+    HIPCHK(c, hipMemcpy(dst, src, (size_t)n * B * sizeof(float), hipMemcpyHostToDevice));
+    return PDBO_OK;
+  }
   std::vector<float> h((size_t)n * B);
   for (int i = 0; i < n; ++i)
     for (int b = 0; b < B; ++b) h[(size_t)i * B + b] = src[(size_t)b * n + i];
@@ -2552,8 +2685,8 @@ pdbo_status qubo_gda_get_state(pdbo_ctx* c, float* x, float* y, int64_t* t) {
   }
   if (c->kind == 3) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    if (x) STCHK(spmm_download(c, c->spmm.X[c->parity], x));
-    if (y) STCHK(spmm_download(c, c->spmm.Y, y));
+    if (x) STCHK(spmm_download(c, c->spmm.X[c->parity], x, !c->spmm.sent));
+    if (y) STCHK(spmm_download(c, c->spmm.Y, y, !c->spmm.sent));
     if (t) *t = c->t_host;
     return PDBO_OK;
   }
@@ -2619,8 +2752,8 @@ pdbo_status qubo_gda_set_state(pdbo_ctx* c, const float* x, const float* y, int6
       if (!std::isfinite(y[i])) return fail(c, PDBO_EINVAL, "y must be finite");
   HIPCHK(c, hipStreamSynchronize(c->stream));
   if (c->kind == 3) {
-    if (x) STCHK(spmm_upload(c, x, c->spmm.X[c->parity]));
-    if (y) STCHK(spmm_upload(c, y, c->spmm.Y));
+    if (x) STCHK(spmm_upload(c, x, c->spmm.X[c->parity], !c->spmm.sent));
+    if (y) STCHK(spmm_upload(c, y, c->spmm.Y, !c->spmm.sent));
     c->t_host = t;
     HIPCHK(c, hipMemcpy(c->spmm.t_dev, &t, sizeof(t), hipMemcpyHostToDevice));
     return PDBO_OK;
@@ -2840,12 +2973,13 @@ pdbo_status qubo_gda_grad(pdbo_ctx* c, const float* x, float* G) {
     if (!(x[i] >= 0.f && x[i] <= 1.f)) return fail(c, PDBO_EINVAL, "x must lie in [0,1]");
   HIPCHK(c, hipStreamSynchronize(c->stream));
   if (c->kind == 3) {  // node-major operand and result
-    STCHK(spmm_upload(c, x, c->gx_scratch));
+    STCHK(spmm_upload(c, x, c->gx_scratch, true));
     SpmmDev d = c->spmm;
     d.X[0] = c->gx_scratch;
+    if (d.sent) d.grid = std::max(1, std::min((n + 4 * d.G - 1) / (4 * d.G), rowpar_grid_cap()));
     HIPCHK(c, launch_spmm(d, 2, 0, c->g_scratch, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    return spmm_download(c, c->g_scratch, G);
+    return spmm_download(c, c->g_scratch, G, true);
   }
   TempDev tx;
   STCHK(temp_upload(c, tx, x, tot * sizeof(float)));
@@ -3105,7 +3239,8 @@ pdbo_status qubo_dual_bound(pdbo_ctx* c, double ybar, int32_t iters, double* low
     HIPCHK(c, launch_cert_csr(c->csr, x0, c->par.scale, ybar, c->cert_rows, c->cert_res, c->stream));
   } else {
     SpmmDev d = c->spmm;
-    d.win = nullptr;  // no incumbent here: the step launches copy nothing
+    d.win = nullptr;   // no incumbent here: the step launches copy nothing
+    d.sent = nullptr;  // one column: the row-parallel kernel
     d.B = 1;
     d.W = 1;
     d.G = 64;

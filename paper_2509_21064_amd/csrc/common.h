@@ -438,6 +438,13 @@ struct SpmmDev {
   int64_t* t_dev;         // completed iterations
   uint64_t* ts0;
   int n, B, kappa, trace_cap;
+  // rowsplit.hip (sent non-null): X and Y are then restart-major [B][n], W = B,
+  // nslices = 1 and grid is the number of row segments of a restart
+  const uint32_t* sent;   // entries, 256 words (4 per lane) a group
+  const int2* smeta;      // [slices][sranges] {first group, groups}; slices: srows / 64 a segment
+  const int32_t* srow;    // [grid srows] row in its segment by position (slice, lane), -1: none
+  int srows;              // rows of a segment, a multiple of 64
+  int srange, sranges;    // columns a range (a multiple of 4), ranges
   int W;                  // restarts per lane group (slice width, <= 64)
   int G;                  // lane groups per wave (64 / W)
   int nslices;            // ceil(B / W)
@@ -457,11 +464,18 @@ struct SpmmDev {
   uint64_t* incw;         // [4] the incumbent's N, 256-bit two's complement
   double* Fd;             // [B] objectives of the last evaluation, rounded to float64
 };
+// element (i, b) of X and Y
+__host__ __device__ inline size_t spmm_at(const SpmmDev& d, int i, int b) {
+  return d.sent ? (size_t)b * d.n + i : (size_t)i * d.B + b;
+}
 constexpr int kMaxDigits = 8;  // 192 bits of fixed point
 // mode 0: gradient, Alg. 1 update into X[parity ^ 1] and Y, and the exact
 // objective of round(X[parity]) into the partials; mode 1: the objective only;
 // mode 2: the gradient only, into G (node-major)
+// with sent set, modes 0 and 1 run rowsplit.hip; mode 2 takes node-major
+// operands either way
 hipError_t launch_spmm(const SpmmDev& d, int mode, int parity, float* G, hipStream_t s);
+hipError_t launch_csr_split(const SpmmDev& d, int mode, int parity, hipStream_t s);
 // Objectives from the partials, first argmin over b, incumbent update for
 // evaluations of x^t with t >= 1 (label: the completed iterations), and, for
 // advance != 0, the iteration counter moves on.  The winning rounded vector

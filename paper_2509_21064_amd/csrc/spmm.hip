@@ -139,6 +139,7 @@ __global__ void __launch_bounds__(kSpmmThreads) spmm_kernel(SpmmDev D, int parit
 
 hipError_t launch_spmm(const SpmmDev& d, int mode, int parity, float* G, hipStream_t s) {
   if (d.ndig > 0) return launch_spmm_real(d, mode, parity, G, s);
+  if (d.sent && mode != 2) return launch_csr_split(d, mode, parity, s);
   const dim3 grid(d.grid), blk(kSpmmThreads);
 #define PDBO_S(GK, M)                                                                  \
   if (d.packed)                                                                        \
@@ -274,7 +275,7 @@ __global__ void __launch_bounds__(kBestThreads) spmm_best_kernel(SpmmDev D, int 
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = min(i0 + u * kBestThreads, D.n - 1);
-        v[u] = X[(size_t)i * D.B + wb];
+        v[u] = X[spmm_at(D, i, wb)];
       }
 #pragma unroll
       for (int u = 0; u < U; ++u)
@@ -297,7 +298,7 @@ __global__ void spmm_init_kernel(const double* __restrict__ x0, SpmmDev D, float
   const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (size_t)D.B * D.n) return;
   const int b = (int)(idx / D.n), i = (int)(idx % D.n);
-  const size_t off = (size_t)i * D.B + b;
+  const size_t off = spmm_at(D, i, b);
   D.X[0][off] = x0 ? (float)x0[idx] : philox_start(seed, (uint32_t)b, (uint32_t)i);
   D.Y[off] = y0;
 }
