@@ -158,11 +158,16 @@ typedef struct {
  *              stored exactly.
  *   eval_every evaluate round(x^t) every eval_every iterations (>= 1); the
  *              persistent CSR and MaxSAT paths require 1.
- *   tile       dense: tile configuration id (0 = default for the shape).
+ *   tile       dense: tile configuration id (0 = default for the shape; few
+ *              tiles then run one wave each on copies of the operands in
+ *              fragment order, the same bits; PDBO_FRAG=0 keeps the tiles).
  *              CSR: PDBO_CSR_RESIDENT (one workgroup per restart for all T
  *              iterations, x in LDS; n <= 32768, quadratic or entropy g),
  *              PDBO_CSR_ROWS (one launch per iteration over all rows, the
- *              restarts of a row in adjacent lanes; any n, any g), or
+ *              restarts of a row in adjacent lanes, or for large instances
+ *              and few restarts a workgroup per restart and row segment with
+ *              x in LDS, the same bits; PDBO_CSR_SPLIT=0 keeps the former; any
+ *              n, any g), or
  *              PDBO_CSR_AUTO (resident when it fits and B >= 128, or with fewer
  *              restarts when its iteration is estimated shorter than two
  *              launches; the run is then bit for bit that of the row-parallel

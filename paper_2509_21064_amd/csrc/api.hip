@@ -115,6 +115,7 @@ struct pdbo_ctx {
   // rounding, per-row terms and the result; per-restart records of the
   // resident CSR kernel and the partial sums of the row-parallel one
   float *cert_x = nullptr, *cert_y = nullptr;
+  const uint8_t* cert_af = nullptr;
   uint8_t *cert_xs = nullptr, *cert_xf = nullptr;
   TileDev* cert_tiles = nullptr;
   int8_t* cert_xr = nullptr;
@@ -982,6 +983,8 @@ pdbo_status frag_shadow(pdbo_ctx* c) {
 // fp32 18.9 / 27.3; the tiles stay where restarts are many: n = 5000, B = 100
 // int8 22.4 / 20.8; n = 3000, B = 200 int8 20.2 / 16.9; n = 1000, B = 1024
 // int8 18.5 / 14.1.  Their copy of A is bounded at 512 MB.
+constexpr int64_t kFragBytes = int64_t(512) << 20;
+
 int frag_choice(const pdbo_ctx* c) {
   const int EB = element_bytes(c->prec);
   const TileCfgInfo& cf = dense_cfg(c->cfg);
@@ -994,7 +997,7 @@ int frag_choice(const pdbo_ctx* c) {
     bytes += (double)I.n * I.ld * EB;
     tiles += (double)((I.n + cf.BM - 1) / cf.BM) * ((I.B + cf.BN - 1) / cf.BN);
   }
-  if (bytes > (double)(512 << 20)) return -1;
+  if (bytes > (double)kFragBytes) return -1;
   double best = 2.0 + nk * chunk * std::ceil(tiles / (256.0 * (size > 1 ? 1 : 3)));
   int id = -1;
   for (int f = 0; f < dense_num_frags(); ++f) {
@@ -3160,8 +3163,25 @@ pdbo_status qubo_dual_bound(pdbo_ctx* c, double ybar, int32_t iters, double* low
     STCHK(dalloc(c, &c->cert_x, 2 * (size_t)ld));
     STCHK(dalloc(c, &c->cert_y, (size_t)ld));
     STCHK(dalloc(c, &c->cert_xs, 2 * (size_t)ld * 4));
-    if (c->kind == 0 && c->frag >= 0) {
-      STCHK(dalloc(c, &c->cert_xf, 2 * 16 * (size_t)ld * element_bytes(c->prec)));
+    // One column: by one-wave tiles, on the context's copy of A in fragment order
+    // or on one made here (n = 10^4, B = 1024 int8, 300 iterations: 27.5 -> 6.8 ms).
+    const char* env = std::getenv("PDBO_FRAG");
+    const int64_t rb = c->kind == 0 ? (int64_t)ld * element_bytes(c->prec) : 0;
+    if (c->kind == 0 && !(env && *env && std::atoi(env) <= 0)) {
+      if (c->frag >= 0) {
+        c->cert_af = c->insts_h[0].Af;
+      } else if ((double)n * rb <= (double)kFragBytes) {
+        uint8_t* af = nullptr;
+        if (dalloc(c, &af, (size_t)roundup(n, 16) * rb) == PDBO_OK) {
+          HIPCHK(c, launch_frag_pack(c->insts_h[0].A, n, rb, !dense_cfg(c->cfg).dma, af, c->stream));
+          c->cert_af = af;
+        } else {
+          c->err.clear();  // no room for the copy: the context's tiles
+        }
+      }
+    }
+    if (c->cert_af) {
+      STCHK(dalloc(c, &c->cert_xf, 2 * 16 * (size_t)rb));
       STCHK(dalloc(c, &c->cert_tiles, (size_t)(n + 15) / 16));
       std::vector<TileDev> tiles;
       for (int m = 0; m < (n + 15) / 16; ++m) tiles.push_back(TileDev{0, 16 * m, 0, m});
@@ -3200,13 +3220,14 @@ pdbo_status qubo_dual_bound(pdbo_ctx* c, double ybar, int32_t iters, double* low
     I.gp.beta = 0.f;
     I.gp.gkind = PDBO_G_QUAD;
     const int EB = element_bytes(c->prec);
+    I.Af = c->cert_af;
     I.Xf[0] = c->cert_xf;
     I.Xf[1] = c->cert_xf ? c->cert_xf + 16 * (size_t)ld * EB : nullptr;
     if (c->prec != PDBO_FP32)
       HIPCHK(c, launch_set_state(x0, nullptr, 1, n, ld, x0, nullptr, I.Xs[0], c->prec, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->scratch_inst_d, &I, sizeof(I), hipMemcpyHostToDevice, c->stream));
     int parity = 0;
-    const bool fr = c->frag >= 0;  // then by one-wave tiles, as the context's steps
+    const bool fr = c->cert_af != nullptr;
     const int staged = !dense_cfg(c->cfg).dma;
     if (fr) HIPCHK(c, launch_frag_pack(I.Xs[0], 1, (int64_t)ld * EB, staged, I.Xf[0], c->stream));
     for (int t = 0; t < iters; ++t) {

@@ -96,3 +96,27 @@ def test_batches_and_graphs(grouped, monkeypatch):
     for got in out[1:]:
         for a, b in zip(got, out[0]):
             assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("tile", [2, 10])
+def test_dual_of_tiled_contexts(tile, prec, monkeypatch):
+    """A context on workgroup tiles takes its certificate's descent by one-wave tiles."""
+    P = require_gpu()
+    q = W.random_dense_qubo(500, -60, 60, W.rng_for(5, 0, 0, 500))
+    out = []
+    for frag in ("0", None):
+        say(f"[frag] dual tile={tile} prec={prec} frag={frag}")
+        if frag is None:
+            monkeypatch.delenv("PDBO_FRAG", raising=False)
+        else:
+            monkeypatch.setenv("PDBO_FRAG", frag)
+        par = W.gda_params("qubo", B=70, T=1, scale=40.0 * 500 ** 0.5, precision=prec, tile=tile, seed=2)
+        ctx = P.qubo_gda_init(q, par, None)
+        ctx.step(3)
+        d = [P.qubo_dual_bound(ctx, 20) for _ in range(2)]
+        ctx.step(3)
+        out.append([e[k] for e in d for k in sorted(e)] + [ctx.objectives(), *ctx.get_state()])
+        ctx.destroy()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
