@@ -2029,7 +2029,13 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
     // instances the automatic choice sends here, and of those sent here by the
     // caller the ones with room for two copies of x and int32 totals, whose
     // variant's name then still tells the size class.
-    const bool two_sums = !seq && res_ok && !(sl_env && std::atoi(sl_env) == 0) &&
+    // csr_persistent keeps what it has staged in LDS of the entropy, whose
+    // logarithms cost the resident kernel more registers than it has (n = 1241,
+    // degree 6, B = 200: 2.0 us an iteration against 4.0), and of more restarts
+    // than CUs, two of which it runs on one (quadratic, B = 388: 2.3 against 2.8)
+    const bool keep = n <= 8192 && csr_entries_in_lds(n, nnz, compact) &&
+                      (p->g_kind != PDBO_G_QUAD || p->B > 256);
+    const bool two_sums = !seq && !keep && res_ok && !(sl_env && std::atoi(sl_env) == 0) &&
                           (p->tile == PDBO_CSR_AUTO || (n <= 8192 && csr_double_buffered(n, nnz, compact)));
     if (compact && n <= 8192 && !(sl_env && std::atoi(sl_env) == 0)) {
       // the interleaved layout of the 1024-thread kernels (slices of 64

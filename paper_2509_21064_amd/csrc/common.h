@@ -387,6 +387,8 @@ struct CsrDev {
   GdaP gp;
 };
 bool csr_double_buffered(int n, int64_t nnz, bool packed);
+// whether csr_persistent stages the packed entries in LDS
+bool csr_entries_in_lds(int n, int64_t nnz, bool packed);
 bool csr_fits(int n, int64_t nnz, bool packed, size_t* lds_bytes);
 const char* csr_variant_name(const CsrDev& d, bool packed);
 hipError_t launch_csr_persistent(const CsrDev& d, bool packed, int64_t t0, int nsteps,

@@ -39,6 +39,10 @@ bool csr_fits(int n, int64_t nnz, bool packed, size_t* lds_bytes) {
   return n <= 32768 && need <= kLdsBudget;
 }
 
+bool csr_entries_in_lds(int n, int64_t nnz, bool packed) {
+  return packed && csr_lds_need(n, nnz, true) <= kLdsBudget;
+}
+
 // whether the 1024-thread kernels have room for two copies of x (the entries
 // counted in CSR order, in LDS when they fit)
 bool csr_double_buffered(int n, int64_t nnz, bool packed) {

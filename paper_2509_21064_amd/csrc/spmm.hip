@@ -166,8 +166,8 @@ constexpr int kBestThreads = 1024;
 constexpr int kPartUnroll = 16;  // partials per lane loaded in one batch
 // The kernel is a chain of latencies: the waves' minima are reduced across
 // lanes rather than one after the other, and batches without partials are
-// skipped by the wave (MIS n = 5 * 10^4, B = 10, 25 partials a restart: 0.9 us
-// an iteration less, 27.4 -> 26.5).
+// skipped by the wave (MIS n = 5 * 10^4, B = 10, 25 partials a restart: 28.3 ->
+// 27.4 us an iteration).
 
 __global__ void __launch_bounds__(kBestThreads) spmm_best_kernel(SpmmDev D, int parity,
                                                                  int advance) {
