@@ -3647,7 +3647,8 @@ static pdbo_status sat_layout(int n, int m, int k, const std::vector<int32_t>& p
               }
               some = l;
               const float wt = (float)(E[k - 1] & 0xffffff);
-              const _Float16 h = (_Float16)((E[k - 1] >> 30) & 1 ? wt : -wt);
+              // (bits of zero mark padding: a clause of weight zero has -0)
+              const _Float16 h = (_Float16)((E[k - 1] >> 30) & 1 && wt != 0.f ? wt : -wt);
               std::memcpy(&at[256 * (k - 1)], &h, 2);
             }
             if (some >= 0)

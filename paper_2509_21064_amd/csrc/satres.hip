@@ -66,8 +66,13 @@ __host__ __device__ inline int sr_word(int c, int w) {
 
 int satres_word(int n, int c, int w) { return c * sr_words(n) + sr_word(c, w); }
 
+// MARKS: the sign bits of the table's x mark changed roundings and are dropped
+// (sat_resident, whose x lies in [0, 1]); otherwise a factor is taken as it is,
+// negative for an x outside the box.
+template <bool MARKS>
 __device__ __forceinline__ float sr_lit(uint32_t idx) {
-  return fabsf(*(const PDBO_AS3 float*)(size_t)(idx << 2));
+  const float v = *(const PDBO_AS3 float*)(size_t)(idx << 2);
+  return MARKS ? fabsf(v) : v;
 }
 
 template <int K> struct SrGroup { su32x2 c[K - 1], w; };
@@ -91,19 +96,22 @@ __device__ __forceinline__ float sr_weight(su32x2 v, int u) {
 // N occurrences of a group: the product of the other literals' factors times
 // the signed weight.  3-SAT adds the four of a full group to four sums and
 // those left over to the first; the other k have one sum, in order (the orders
-// of the kernels in maxsat.hip).
-template <int K, int N>
+// of the kernels in maxsat.hip).  Without MARKS the factors may be anything, NaN
+// and infinities included, and what a padding entry (weight bits all zero; a
+// clause of weight zero has the sign bit set) gathered is left out.
+template <int K, int N, bool MARKS>
 __device__ __forceinline__ void sr_terms(const SrGroup<K>& g, float (&s)[4]) {
   float f[N][K - 1];
 #pragma unroll
   for (int u = 0; u < N; ++u)
 #pragma unroll
-    for (int o = 0; o < K - 1; ++o) f[u][o] = sr_lit(sr_half(g.c[o], u));
+    for (int o = 0; o < K - 1; ++o) f[u][o] = sr_lit<MARKS>(sr_half(g.c[o], u));
 #pragma unroll
   for (int u = 0; u < N; ++u) {
     float prod = f[u][0];
 #pragma unroll
     for (int o = 1; o < K - 1; ++o) prod *= f[u][o];
+    if constexpr (!MARKS) prod = sr_half(g.w, u) != 0u ? prod : 0.f;
     float& a = s[K == 3 && N == 4 ? u : 0];
     a = fmaf(sr_weight(g.w, u), prod, a);
   }
@@ -112,7 +120,7 @@ __device__ __forceinline__ void sr_terms(const SrGroup<K>& g, float (&s)[4]) {
 // Adjoint sums of the wave's slices j = 0..: next() moves cur on to the next
 // group, across slices, so that its entries are on their way while the gathers
 // of the present one run.
-template <int K>
+template <int K, bool MARKS>
 struct SrWalk {
   const PDBO_AS1 uint32_t* ent;
   const PDBO_AS4 int* slices;  // {first word, full groups << 1 | a group is left over}
@@ -139,20 +147,21 @@ struct SrWalk {
     for (int g = 0; g < nf; ++g) {
       const SrGroup<K> c = cur;
       cur = sr_load<K>(g + 1 < ng ? at(sl, g + 1) : at(nx, 0));
-      sr_terms<K, 4>(c, s);
+      sr_terms<K, 4, MARKS>(c, s);
     }
     if (sl.y & 1) {
       const SrGroup<K> c = cur;
       cur = sr_load<K>(at(nx, 0));
-      sr_terms<K, 3>(c, s);
+      sr_terms<K, 3, MARKS>(c, s);
     }
     return K == 3 ? (s[0] + s[1]) + (s[2] + s[3]) : s[0];
   }
 };
 
-// g and g' of the entropy at the same x, with two logarithms: g is 0 at 0 and
-// 1, and g' is constant where its clip moves x (lo, hi: its values there).  Same
-// values as g_value and g_deriv.
+// g and g' of the entropy at the same x, with two logarithms: a term of g is 0
+// where its argument is not positive, and g' is constant where its clip moves x
+// (lo, hi: its values there; lo for a NaN too).  Same values as g_value and
+// g_deriv, for every x; with BOX for x in [0, 1], where g is 0 at both ends.
 struct GEnds {
   float lo, hi;
 };
@@ -160,19 +169,28 @@ template <int GK>
 __device__ __forceinline__ GEnds g_ends() {
   return GK == 0 ? GEnds{0.f, 0.f} : GEnds{g_deriv(0.f, 1), g_deriv(1.f, 1)};
 }
-template <int GK>
+template <int GK, bool BOX>
 __device__ __forceinline__ void g_both(float x, GEnds e, float& gv, float& gd) {
   if constexpr (GK == 0) {
     gv = g_value(x, 0);
     gd = g_deriv(x, 0);
   } else {
 #pragma clang fp contract(off)  // g is the sum of two rounded products
-    const bool in = x > 0.f && x < 1.f;
-    const float xi = in ? x : 0.5f;
-    const float l0 = logf(xi), l1 = logf(1.f - xi);
-    const float a = xi * l0, c = (1.f - xi) * l1;
-    gv = in ? a + c : 0.f;
-    gd = x < kEntropyEps ? e.lo : x > 1.f - kEntropyEps ? e.hi : l0 - l1;
+    if constexpr (BOX) {
+      const bool in = x > 0.f && x < 1.f;
+      const float xi = in ? x : 0.5f;
+      const float l0 = logf(xi), l1 = logf(1.f - xi);
+      const float a = xi * l0, c = (1.f - xi) * l1;
+      gv = in ? a + c : 0.f;
+      gd = x < kEntropyEps ? e.lo : x > 1.f - kEntropyEps ? e.hi : l0 - l1;
+    } else {
+      const bool p0 = x > 0.f, p1 = x < 1.f;
+      const float x0 = p0 ? x : 1.f, x1 = p1 ? 1.f - x : 1.f;
+      const float l0 = logf(x0), l1 = logf(x1);
+      const float a = p0 ? x0 * l0 : 0.f, c = p1 ? x1 * l1 : 0.f;
+      gv = a + c;
+      gd = !(x >= kEntropyEps) ? e.lo : x > 1.f - kEntropyEps ? e.hi : l0 - l1;
+    }
   }
 }
 
@@ -282,8 +300,8 @@ __global__ void __launch_bounds__(kSrThreads)
     improved = true;
   };
 
-  SrWalk<K> walk{(const PDBO_AS1 uint32_t*)D.pent, (const PDBO_AS4 int*)D.pslice, wid, 2 * lane,
-                 (n + 63) / 64, {}};
+  SrWalk<K, true> walk{(const PDBO_AS1 uint32_t*)D.pent, (const PDBO_AS4 int*)D.pslice, wid, 2 * lane,
+                       (n + 63) / 64, {}};
   // 16 lanes to each changed variable, over its occurrences
   auto count_changes = [&](int cnt) {
     long long d = 0;
@@ -353,7 +371,7 @@ __global__ void __launch_bounds__(kSrThreads)
       const int p = tv + j * kSrThreads;
       const float x = fabsf(tab[2 * min(p, n - 1)]);  // lanes past n: unused
       float gv, gd;
-      g_both<GK>(x, ends, gv, gd);
+      g_both<GK, true>(x, ends, gv, gd);
       // one coordinate of Alg. 1, as gda_update
       const float y = yr.v[j], dL = fmaf(y, gd, grad);
       float a = fminf(fmaxf(fmaf(-gp.alpha, dL, x), 0.f), 1.f);
@@ -466,8 +484,8 @@ __global__ void __launch_bounds__(kSrThreads)
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int b = blockIdx.x, n = D.n;
   const float* xb = X + (size_t)b * ldx;
-  SrWalk<K> walk{(const PDBO_AS1 uint32_t*)D.pent, (const PDBO_AS4 int*)D.pslice, wid, 2 * lane,
-                 (n + 63) / 64, {}};
+  SrWalk<K, false> walk{(const PDBO_AS1 uint32_t*)D.pent, (const PDBO_AS4 int*)D.pslice, wid, 2 * lane,
+                        (n + 63) / 64, {}};
   walk.start();
   for (int i = tid; i < n; i += kSrThreads) {
     const int p = D.pos[i];
@@ -497,7 +515,7 @@ __global__ void __launch_bounds__(kSrThreads)
       dx[(size_t)b * ldo + i] = tab[i];
     } else {
       float gv, gd;
-      g_both<GK>(xb[i], ends, gv, gd);
+      g_both<GK, false>(xb[i], ends, gv, gd);
       dx[(size_t)b * ldo + i] = scale * fmaf(Yv[(size_t)b * ldx + i], gd, tab[i]);
       dy[(size_t)b * ldo + i] = scale * gv;
     }
@@ -586,7 +604,7 @@ __global__ void __launch_bounds__(kSrThreads)
   const GEnds ends = g_ends<GK>();
   for (int i = tid; i < n; i += kSrThreads) {
     float gv, gd;
-    g_both<GK>(xb[i], ends, gv, gd);
+    g_both<GK, false>(xb[i], ends, gv, gd);
     acc += (double)yb[i] * (double)gv;
   }
   for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);

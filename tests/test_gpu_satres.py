@@ -77,3 +77,47 @@ def test_lagrangian_matches_general_kernels(n, ratio, k, wmax, alpha, monkeypatc
             ctx.destroy()
         for a, b in zip(*out):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n,m,k,wmax", [(64, 270, 3, 9), (65, 140, 2, 5), (1025, 4000, 4, 10), (2049, 8000, 3, 10),
+                                        (4097, 20000, 5, 7), (16385, 30000, 3, 10)])
+def test_lagrangian_outside_the_box_matches_general_kernels(n, m, k, wmax, monkeypatch):
+    """x outside [0, 1] (the step of an optimizer that clamps afterwards), clauses
+    of weight zero, and an x with NaN and infinities, which reach the variables
+    that share a clause with them and no others."""
+    import torch
+    P = require_gpu()
+    f = W.random_maxsat(n, m, k, 0, wmax, np.random.default_rng([n, k]))
+    f.w[::7] = 0
+    nb = 3
+    g = np.random.default_rng(4)
+    x0 = g.uniform(-0.2, 1.2, (nb, n)).astype(np.float32)
+    x0[:, ::9], x0[:, 1::11], x0[:, 2::13] = 0.0, 1.0, np.nextafter(np.float32(1), np.float32(2))
+    x0[2, 3], x0[2, 5], x0[2, n - 1] = np.nan, np.inf, -np.inf
+    y0 = g.uniform(-1, 2, (nb, n)).astype(np.float32)
+    x, y = torch.from_numpy(x0).cuda(), torch.from_numpy(y0).cuda()
+    w = torch.tensor([0.75, -2.0, 1.0], device="cuda")
+    for kind in ("entropy", "quad"):
+        say(f"[satres outside] n={n} k={k} g={kind}")
+        out = []
+        for res in ("1", "0"):
+            monkeypatch.setenv("PDBO_SAT_RESIDENT", res)
+            ctx = P.maxsat_gda_init(f, W.gda_params("maxsat", B=1, T=1, scale=2.0, g=kind), None)
+            L = P.maxsat_lagrangian_fwd(ctx, x, y)
+            out.append([v.cpu().numpy() for v in (L, *P.maxsat_lagrangian_bwd(ctx, x, y, w))])
+            ctx.destroy()
+        for a, b in zip(*out):
+            assert np.array_equal(a, b, equal_nan=True)
+        assert np.isfinite(out[0][1][:2]).all() and 0 < np.isfinite(out[0][1][2]).sum() < n
+        if kind == "quad":
+            # the multilinear extension in float64: at most 1.2^(k-1) per factor
+            # product, k + occurrences roundings of 2^-24 each
+            X = torch.from_numpy(x0[:2].astype(np.float64)).requires_grad_()
+            Y = torch.from_numpy(y0[:2].astype(np.float64))
+            v, neg = torch.from_numpy(np.abs(f.lits) - 1).long(), torch.from_numpy(f.lits < 0)
+            fac = torch.where(neg, X[:, v], 1 - X[:, v]).prod(-1)
+            val = (fac * torch.from_numpy(f.w.astype(np.float64))).sum(-1) / 2.0 + (Y * (X * X - X)).sum(-1)
+            (val * torch.tensor([0.75, -2.0], dtype=torch.float64)).sum().backward()
+            occ = np.bincount(np.abs(f.lits).ravel() - 1, minlength=n).max()
+            tol = 2.0 * (occ * wmax * 1.2 ** (k - 1) / 2.0 + 3.0) * (occ + k + 4) * 2.0 ** -24
+            assert np.abs(out[0][1][:2] - X.grad.numpy()).max() <= tol
