@@ -171,12 +171,13 @@ typedef struct {
  *              PDBO_CSR_AUTO (resident when it fits and B >= 128, or with fewer
  *              restarts when its iteration is estimated shorter than two
  *              launches; the run is then bit for bit that of the row-parallel
- *              path, its trace included, and graph_chunk has nothing to do).  With
- *              n <= 8192 the resident kernel stages its packed entries
- *              interleaved by slices of 64 rows when that takes no more LDS
- *              than CSR order, and instances with weights up to 2048 stage
- *              them by position (same sums in the same order, so the same
- *              results); PDBO_CSR_SLICED=0 keeps CSR order.
+ *              path, its trace included, and graph_chunk has nothing to do).
+ *              PDBO_CSR_RESIDENT runs csr_persistent, which with n <= 8192
+ *              stages its packed entries interleaved by slices of 64 rows when
+ *              that takes no more LDS than CSR order; PDBO_CSR_AUTO may take
+ *              csr_resident instead (n <= 16384, weights up to 2048, entries by
+ *              position: same sums in the same order, so the same results).
+ *              PDBO_CSR_SLICED=0 keeps csr_persistent and CSR order.
  *   graph_chunk  dense and row-parallel CSR paths: 0 = eager launches;
  *              K > 0 (even) = capture K iterations in one hipGraph and replay it.
  *   g_degree   d of PDBO_G_POLY, in [1, 16]; ignored for the other kinds.
@@ -482,8 +483,9 @@ PDBO_API pdbo_status pdbo_autotune_store(const char* key, int32_t cfg);
 PDBO_API pdbo_status pdbo_autotune_lookup(const char* key, int32_t* cfg);
 
 /* Name of the tile configuration the dense path uses, of the kernel variant
- * the restart-resident CSR path uses, or "csr_rows" for the row-parallel CSR
- * path (static string; empty for the other paths). */
+ * the restart-resident CSR path runs ("csr_resident", "csr_resident_seq" for
+ * few restarts, else a variant of csr_persistent), or "csr_rows" or "csr_split"
+ * for the row-parallel CSR path (static string; empty for the other paths). */
 PDBO_API const char* pdbo_tile_name(const pdbo_ctx* ctx);
 
 PDBO_API void pdbo_destroy(pdbo_ctx* ctx);

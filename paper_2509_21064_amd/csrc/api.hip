@@ -2025,10 +2025,8 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
       d.packed = dp;
     }
     const char* sl_env = std::getenv("PDBO_CSR_SLICED");
-    // The resident kernel runs the same sums as csr_persistent.  It takes the
-    // instances the automatic choice sends here, and of those sent here by the
-    // caller the ones with room for two copies of x and int32 totals, whose
-    // variant's name then still tells the size class.
+    // The automatic choice may take the resident kernel, which runs the same sums
+    // as csr_persistent; PDBO_CSR_RESIDENT names the latter.
     // csr_persistent keeps what it has staged in LDS of the entropy, whose
     // logarithms cost the resident kernel more registers than it has (n = 1241,
     // degree 6, B = 200: 2.0 us an iteration against 4.0), and of more restarts
@@ -2036,8 +2034,8 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
     const bool keep = n <= 8192 && csr_entries_in_lds(n, nnz, compact) &&
                       (p->g_kind != PDBO_G_QUAD || p->B > 256);
     const bool two_sums = !seq && !keep && res_ok && !(sl_env && std::atoi(sl_env) == 0) &&
-                          (p->tile == PDBO_CSR_AUTO || (n <= 8192 && csr_double_buffered(n, nnz, compact)));
-    if (compact && n <= 8192 && !(sl_env && std::atoi(sl_env) == 0)) {
+                          p->tile == PDBO_CSR_AUTO;
+    if (compact && n <= 8192 && !seq && !two_sums && !(sl_env && std::atoi(sl_env) == 0)) {
       // the interleaved layout of the 1024-thread kernels (slices of 64
       // positions, each as long as its longest row), used when it takes no
       // more LDS than row_ptr and the entries in CSR order
@@ -2052,9 +2050,7 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
         tot += (int64_t)64 * lmax;
       }
       auto a16 = [](int64_t v) { return (v + 15) / 16 * 16; };
-      const bool sliced = a16(4 * tot) <= a16(4 * (int64_t)(n + 1)) + a16(4 * nnz);
-      d.sliced = sliced ? 1 : 0;
-      if (sliced && !seq && !two_sums) {
+      if (a16(4 * tot) <= a16(4 * (int64_t)(n + 1)) + a16(4 * nnz)) {
         psl.assign((size_t)tot, 0u);
         for (int q = 0; q < n; ++q) {
           const int i = order[q];

@@ -371,7 +371,6 @@ struct CsrDev {
   // contexts that stand in for the row-parallel path: its order of the sums,
   // and its incumbent and trace, kept on the device (else null)
   int seq;
-  int sliced;             // the interleaved layout takes no more LDS than CSR order (psl above)
   int trace_cap;
   TraceRec* rtr;          // [B][kResTrace] the restarts' own improvements in one launch
   int32_t* rtl;           // [B] their number
@@ -386,7 +385,6 @@ struct CsrDev {
   float kos;
   GdaP gp;
 };
-bool csr_double_buffered(int n, int64_t nnz, bool packed);
 // whether csr_persistent stages the packed entries in LDS
 bool csr_entries_in_lds(int n, int64_t nnz, bool packed);
 bool csr_fits(int n, int64_t nnz, bool packed, size_t* lds_bytes);

@@ -43,13 +43,6 @@ bool csr_entries_in_lds(int n, int64_t nnz, bool packed) {
   return packed && csr_lds_need(n, nnz, true) <= kLdsBudget;
 }
 
-// whether the 1024-thread kernels have room for two copies of x (the entries
-// counted in CSR order, in LDS when they fit)
-bool csr_double_buffered(int n, int64_t nnz, bool packed) {
-  const bool pk = packed && csr_lds_need(n, nnz, true) <= kLdsBudget;
-  return csr_lds_need(n, nnz, pk) + align16((size_t)n * 4) <= kLdsBudget;
-}
-
 // sum_k Ahat_ik x_k (float) and sum_k Ahat_ik [x_k > 1/2] (int) over row i,
 // four entries at a time so that their LDS reads are in flight together.
 template <bool PACKED>
@@ -415,16 +408,15 @@ static hipError_t launch_csr_r(const CsrDev& d, int64_t t0, int nsteps, hipStrea
 // or updated in place, int32 or int64 wave sums (and, double-buffered, int32
 // totals: "t32"), and beyond 8192 rows 512 threads with 32 or 64 rows each.
 const char* csr_variant_name(const CsrDev& d, bool packed) {
-  if (d.seq) return "csr_resident_seq";
+  if (d.rent) return d.seq ? "csr_resident_seq" : "csr_resident";
   const bool pk = packed && csr_lds_need(d.n, d.nnz, true) <= kLdsBudget;
-  if (d.rent && (d.n > 8192 || !csr_double_buffered(d.n, d.nnz, packed))) return "csr_resident";
   if ((d.n + 1023) / 1024 > 8) {
     const bool r32 = (d.n + 511) / 512 <= 32;
     return pk ? (r32 ? "csr_packed_rows32" : "csr_packed_rows64")
               : (r32 ? "csr_l2_rows32" : "csr_l2_rows64");
   }
-  const bool dbuf = csr_double_buffered(d.n, d.nnz, packed);
-  const bool sl = pk && (d.psl || (d.rent && d.sliced));
+  const bool dbuf = csr_lds_need(d.n, d.nnz, pk) + align16((size_t)d.n * 4) <= kLdsBudget;
+  const bool sl = pk && d.psl;
   if (dbuf && d.tot32) return sl ? "csr_sliced_dbuf_t32" : pk ? "csr_packed_dbuf_t32" : "csr_l2_dbuf_t32";
   static const char* names[3][2][2] = {
       {{"csr_l2_inplace_i64", "csr_l2_inplace_i32"}, {"csr_l2_dbuf_i64", "csr_l2_dbuf_i32"}},

@@ -118,3 +118,23 @@ def test_long_call_set_state_and_restart():
     for a, b in zip(*out):
         for u, v in zip(a, b) if isinstance(a, tuple) else [(a, b)]:
             assert np.array_equal(u, v)
+
+
+@pytest.mark.parametrize("n,deg,wmax,B,auto,forced", [
+    (300, 6, 1, 128, "csr_resident", "csr_packed_dbuf_t32"), (2000, 6, 3, 128, "csr_resident", "csr_sliced_dbuf_t32"),
+    (2000, 60, 1, 130, "csr_resident", "csr_l2_dbuf_t32"), (2000, 6, 3, 300, "csr_sliced_dbuf_t32", "csr_sliced_dbuf_t32"),
+    (2000, 6, 2049, 128, "csr_sliced_dbuf_t32", "csr_sliced_dbuf_t32")])
+def test_name_tells_the_kernel(n, deg, wmax, B, auto, forced):
+    """The automatic choice may take csr_resident, a caller who names the
+    restart-resident path gets csr_persistent (whose variants for quadratic g and
+    int32 totals keep a test that way); the name tells which, the bits do not."""
+    P = require_gpu()
+    q = _graph(n, deg, 4, wmax)
+    x0 = W.x0_uniform(9, 4, B, n)
+    say(f"[resident name] n={n} deg={deg} wmax={wmax} B={B}")
+    p = W.gda_params("qubo", B=B, T=1, scale=float(wmax))
+    a, name = _run(P, q, p, x0, [40])
+    b, named = _run(P, q, dict(p, tile=1), x0, [1, 39])
+    assert (name, named) == (auto, forced)
+    _same(a, b)
+    assert np.array_equal(a["F"], oq.objective(q, a["x"] > 0.5))
