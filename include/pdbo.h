@@ -177,7 +177,8 @@ typedef struct {
  *              that takes no more LDS than CSR order; PDBO_CSR_AUTO may take
  *              csr_resident instead (n <= 16384, weights up to 2048, entries by
  *              position: same sums in the same order, so the same results).
- *              PDBO_CSR_SLICED=0 keeps csr_persistent and CSR order.
+ *              PDBO_CSR_SLICED=0 keeps csr_persistent and CSR order;
+ *              PDBO_CSR_RESIDENT=0 never takes csr_resident, 1 wherever it can.
  *   graph_chunk  dense and row-parallel CSR paths: 0 = eager launches;
  *              K > 0 (even) = capture K iterations in one hipGraph and replay it.
  *   g_degree   d of PDBO_G_POLY, in [1, 16]; ignored for the other kinds.

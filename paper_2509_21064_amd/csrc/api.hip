@@ -37,17 +37,27 @@ constexpr int kMaxLimbs = 4;  // int8 limbs of the dense exact evaluation
 // there are enough restarts to occupy the chip
 constexpr int kResidentMinB = 128;
 // and, with fewer, when an iteration of the resident kernel is estimated
-// shorter than the row-parallel path's two launches.  Measured (us an
-// iteration, resident against row-parallel, B = 10): n = 1000, degree 3:
-// 0.7 / 11.1; n = 8000, degree 12: 8.4 / 12.4; n = 16000, degree 3: 8.7 / 12.6,
-// degree 12: 17.8 / 13.8; degree 100: n = 2000 7.8 / 16.2, n = 4000 15.4 / 16.5,
-// n = 16000 144 / 24.  B = 100: n = 2000, degree 6: 1.5 / 26; n = 16000,
-// degree 12: 18 / 49.
-double resident_us(int n, int64_t words) {
-  const double per_word = n > 8192 ? 9e-5 : n > 4096 ? 7e-5 : 4e-5;
-  return 0.4 + 2.5e-4 * n + per_word * (double)words;
+// shorter than the row-parallel path's two launches.  Fitted to (us an iteration
+// over the first 500, resident against row-parallel; quadratic g, B = 10): n =
+// 1000, degree 100: 8.7 / 16.2; n = 2000, degree 6: 1.7 / 9.8, 60: 9.7 / 13.7,
+// 100: 15.0 / 16.4; n = 4000, degree 12: 5.7 / 10.6, 40: 13.7 / 12.6, 100: 30 /
+// 16.9; n = 8000, degree 12: 10.6 / 11.7; n = 16000, degree 12: 22.3 / 13.2.
+// B = 100: n = 2000, degree 6: 1.8 / 26; n = 4000, degree 100: 31 / 44; n =
+// 16000, degree 12: 22.6 / 50.  Entropy, B = 10: n = 2000, degree 60: 15.3 /
+// 13.6; n = 4000, degree 12: 8.4 / 10.4; n = 8000, degree 3: 10.3 / 10.3; n =
+// 12000, degree 3: 18.0 / 10.7; B = 100: n = 12000, degree 3: 18.1 / 36.
+double resident_us(int n, int64_t words, int g_kind) {
+  const double per_word = n > 8192 ? 9e-5 : n > 4096 ? 7e-5 : csr_resident_staged(n, words) ? 4e-5 : 7.2e-5;
+  const double us = 0.4 + 2.5e-4 * n + per_word * (double)words;
+  return g_kind == PDBO_G_QUAD ? us : 1.0 + 0.4 * csr_resident_rows(n) + 1.3 * us;
 }
-double rowpar_us(int B) { return 9.0 + 0.1 * B; }
+double rowpar_us(int n, int64_t nnz, int B) {
+  return 9.0 + 0.1 * B + 4e-6 * (double)n * B + std::max(0.07 * (double)nnz / n, 5e-7 * (double)nnz * B);
+}
+// Up to this many restarts the resident kernel stays with the entropy beyond
+// 8192 rows too, where the estimate is against it: its runs are compared with
+// the row-parallel path's there.
+constexpr int kEntropyResidentB = 5;
 constexpr int64_t kI64Max = LLONG_MAX;
 
 int roundup(int v, int a) { return (v + a - 1) / a * a; }
@@ -1961,11 +1971,17 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
                       n <= 16384 && persistent_ok(p);
   const bool few = path == PDBO_CSR_AUTO && p->B < kResidentMinB;
   const int64_t res_words = res_ok ? res_layout_words(n, C.rp.data(), order, nullptr) : 0;
+  // PDBO_CSR_RESIDENT: 0 never takes csr_resident, 1 wherever it can
+  const char* res_env = std::getenv("PDBO_CSR_RESIDENT");
+  const int force = res_env && *res_env ? std::atoi(res_env) : -1;
   bool seq = false;
   if (path == PDBO_CSR_AUTO) {
     if (fits && p->B >= kResidentMinB && persistent_ok(p)) {
       path = PDBO_CSR_RESIDENT;
-    } else if (res_ok && few && resident_us(n, res_words) < rowpar_us(p->B)) {
+    } else if (res_ok && few && force != 0 &&
+               (force == 1 || resident_us(n, res_words, p->g_kind) < rowpar_us(n, (int64_t)C.col.size(), p->B) ||
+                (n > 8192 && p->B <= kEntropyResidentB &&
+                 resident_us(n, res_words, PDBO_G_QUAD) < rowpar_us(n, (int64_t)C.col.size(), p->B)))) {
       path = PDBO_CSR_RESIDENT;
       seq = true;
     } else {
@@ -2027,14 +2043,28 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
     const char* sl_env = std::getenv("PDBO_CSR_SLICED");
     // The automatic choice may take the resident kernel, which runs the same sums
     // as csr_persistent; PDBO_CSR_RESIDENT names the latter.
-    // csr_persistent keeps what it has staged in LDS of the entropy, whose
-    // logarithms cost the resident kernel more registers than it has (n = 1241,
-    // degree 6, B = 200: 2.0 us an iteration against 4.0), and of more restarts
-    // than CUs, two of which it runs on one (quadratic, B = 388: 2.3 against 2.8)
+    // csr_persistent keeps of what it has staged in LDS (us an iteration over the
+    // first 200 / 2000, csr_resident against csr_persistent):
+    // - the entropy: n = 300, degree 3, B = 128: 2.0 / 1.0 over 200; n = 2000,
+    //   degree 6, B = 256: 4.8 / 2.7; n = 5000, degree 5, B = 128: 11.3 and 8.2 /
+    //   5.4 and 5.1;
+    // - more restarts than CUs, two of which it runs on one: n = 2000, degree 6,
+    //   B = 400: 3.4 / 3.0 over 200;
+    // - more than 4096 rows: n = 5000, degree 3, B = 256: 3.9 and 2.9 / 3.1 and
+    //   2.7; n = 8000, degree 2: 4.1 and 3.0 / 4.0 and 3.4.
+    // With up to 4096 rows csr_resident is behind in a run's first iterations,
+    // when most waves have rounding changes to count, and ahead of it over 1000
+    // (n = 4000, degree 4, B = 256, over 100, 200, 1000: 3.9, 3.2, 2.1 / 2.9, 2.7,
+    // 2.4; n = 2000, degree 6: 1.8 / 2.0 over 200).  Entries that csr_persistent
+    // reads through L2 are always better off on csr_resident, or equal (entropy,
+    // n = 8000, degree 3, B = 128: 12.0 and 8.8 / 11.5 and 11.1; quadratic, n =
+    // 4000, degree 12, B = 256: 6.1 / 32; n = 16000, degree 3, B = 400: 19 / 133),
+    // and so is everything beyond 8192 rows (n = 9000, degree 1, B = 256,
+    // entropy: 13 / 24).
     const bool keep = n <= 8192 && csr_entries_in_lds(n, nnz, compact) &&
-                      (p->g_kind != PDBO_G_QUAD || p->B > 256);
-    const bool two_sums = !seq && !keep && res_ok && !(sl_env && std::atoi(sl_env) == 0) &&
-                          p->tile == PDBO_CSR_AUTO;
+                      (p->g_kind != PDBO_G_QUAD || p->B > 256 || n > 4096);
+    const bool two_sums = p->tile == PDBO_CSR_AUTO && !seq && res_ok && force != 0 && (force == 1 || !keep) &&
+                          !(sl_env && std::atoi(sl_env) == 0);
     if (compact && n <= 8192 && !seq && !two_sums && !(sl_env && std::atoi(sl_env) == 0)) {
       // the interleaved layout of the 1024-thread kernels (slices of 64
       // positions, each as long as its longest row), used when it takes no

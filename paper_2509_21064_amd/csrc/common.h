@@ -395,6 +395,7 @@ hipError_t launch_csr_persistent(const CsrDev& d, bool packed, int64_t t0, int n
 constexpr int kResTrace = 1024;  // records per restart and launch
 int csr_resident_rows(int n);    // positions per thread, 0 when n is too large
 int csr_resident_copies(int n);  // copies of x in LDS
+bool csr_resident_staged(int n, int64_t nrent);  // whether the entries are staged in LDS
 int csr_resident_word(int n, int c, int p);  // word of position p in copy c
 // Incumbent and trace from the restarts' own improvements in a launch of nsteps
 // iterations; advances *t_dev.

@@ -441,6 +441,8 @@ static size_t csr_resident_lds(int n, int64_t nrent, bool ents) {
          (csr_resident_rows(n) <= 4 ? (size_t)csr_resident_rows(n) * kResThreads * 4 : 0);
 }
 
+bool csr_resident_staged(int n, int64_t nrent) { return csr_resident_lds(n, nrent, true) <= kResLds; }
+
 template <int R, bool SEQ, int GK, bool LDSE>
 static hipError_t launch_res_k(const CsrDev& d, int64_t t0, int nsteps, hipStream_t s) {
   auto kern = csr_resident<R, SEQ, GK, LDSE>;
@@ -453,7 +455,7 @@ static hipError_t launch_res_k(const CsrDev& d, int64_t t0, int nsteps, hipStrea
 
 template <int R, int GK>
 static hipError_t launch_res_r(const CsrDev& d, int64_t t0, int nsteps, hipStream_t s) {
-  const bool in_lds = csr_resident_lds(d.n, d.nrent, true) <= kResLds;
+  const bool in_lds = csr_resident_staged(d.n, d.nrent);
   if (d.seq)
     return in_lds ? launch_res_k<R, true, GK, true>(d, t0, nsteps, s)
                   : launch_res_k<R, true, GK, false>(d, t0, nsteps, s);

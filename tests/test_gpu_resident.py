@@ -138,3 +138,42 @@ def test_name_tells_the_kernel(n, deg, wmax, B, auto, forced):
     assert (name, named) == (auto, forced)
     _same(a, b)
     assert np.array_equal(a["F"], oq.objective(q, a["x"] > 0.5))
+
+
+@pytest.mark.parametrize("n,deg,B,g,name", [
+    (5000, 3, 128, "quad", "csr_sliced_dbuf_t32"), (7000, 3, 130, "quad", "csr_sliced_inplace_i32"),
+    (4000, 4, 128, "quad", "csr_resident"), (9000, 1, 128, "entropy", "csr_resident"),
+    (8000, 3, 128, "entropy", "csr_resident"), (2000, 6, 128, "entropy", "csr_sliced_dbuf_t32"),
+    (4000, 40, 10, "quad", "csr_rows"), (2000, 60, 10, "quad", "csr_resident_seq"),
+    (2000, 60, 10, "entropy", "csr_rows"), (12000, 3, 10, "entropy", "csr_rows"),
+    (12000, 3, 10, "quad", "csr_resident_seq"), (12000, 3, 100, "entropy", "csr_resident_seq")])
+def test_automatic_choice(n, deg, B, g, name, monkeypatch):
+    """What the measured times choose, on both sides of each line."""
+    P = require_gpu()
+    monkeypatch.setenv("PDBO_ROUTE", "0")
+    q = W.maxcut_c2(2, n=n, M=n * deg // 2)
+    say(f"[resident choice] n={n} deg={deg} B={B} g={g}")
+    ctx = P.qubo_gda_init(q, W.gda_params("maxcut", B=B, T=1, g=g), None)
+    got = ctx.tile_name
+    ctx.destroy()
+    assert got == name
+
+
+@pytest.mark.parametrize("n,deg,wmax,hub,even", SIZES)
+def test_forced_resident_matches_persistent(n, deg, wmax, hub, even, monkeypatch):
+    """csr_resident in csr_persistent's order wherever it can run, staged or
+    streamed, with either g."""
+    P = require_gpu()
+    q = _graph(n, deg, 6, wmax, hub, even)
+    B = 130
+    x0 = W.x0_uniform(9, 6, B, n)
+    x0[:, ::11] = 0.5
+    for g in ("quad", "entropy"):
+        say(f"[resident forced] n={n} deg={deg} wmax={wmax} hub={hub} g={g}")
+        p = W.gda_params("qubo", B=B, T=1, scale=float(max(1, wmax)), g=g)
+        out = []
+        for force in ("1", "0"):
+            monkeypatch.setenv("PDBO_CSR_RESIDENT", force)
+            out.append(_run(P, q, p, x0, [2, 38]))
+        assert out[0][1] == "csr_resident" and not out[1][1].startswith("csr_resident")
+        _same(out[0][0], out[1][0])
