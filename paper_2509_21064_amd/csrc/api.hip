@@ -130,6 +130,7 @@ struct pdbo_ctx {
   const uint8_t* cert_af = nullptr;
   uint8_t *cert_xs = nullptr, *cert_xf = nullptr;
   TileDev* cert_tiles = nullptr;
+  bool cert_frag = false;  // cert_af, cert_xf and cert_tiles are complete
   int8_t* cert_xr = nullptr;
   double *cert_rows = nullptr, *cert_res = nullptr;
   int64_t *cert_i64 = nullptr;
@@ -177,7 +178,9 @@ pdbo_status fail(pdbo_ctx* c, pdbo_status s, const std::string& msg) {
   return s;
 }
 
+// (the error is consumed: a launcher's hipGetLastError would report it again)
 pdbo_status hipfail(pdbo_ctx* c, const char* what, hipError_t e) {
+  (void)hipGetLastError();
   std::string m = std::string(what) + ": " + hipGetErrorName(e) + " (" + hipGetErrorString(e) + ")";
   return fail(c, e == hipErrorOutOfMemory ? PDBO_ENOMEM : PDBO_EDEVICE, m);
 }
@@ -197,8 +200,8 @@ pdbo_status hipfail(pdbo_ctx* c, const char* what, hipError_t e) {
 template <typename T>
 pdbo_status dalloc(pdbo_ctx* c, T** p, size_t count) {
   *p = nullptr;
-  if (inject_alloc_failure()) return fail(c, PDBO_ENOMEM, "injected allocation failure");
-  const size_t bytes = std::max<size_t>(count * sizeof(T), 16);
+  size_t bytes = std::max<size_t>(count * sizeof(T), 16);
+  if (inject_alloc_failure()) bytes = size_t(1) << 50;  // more than any device has
   void* q = nullptr;
   hipError_t e = hipMalloc(&q, bytes);
   if (e != hipSuccess) return hipfail(c, "hipMalloc", e);
@@ -3220,41 +3223,46 @@ pdbo_status qubo_dual_bound(pdbo_ctx* c, double ybar, int32_t iters, double* low
   const int n = c->n_of[0];
   const int ld = roundup(n, kLdAlign);
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  if (!c->cert_x) {
-    STCHK(dalloc(c, &c->cert_x, 2 * (size_t)ld));
-    STCHK(dalloc(c, &c->cert_y, (size_t)ld));
-    STCHK(dalloc(c, &c->cert_xs, 2 * (size_t)ld * 4));
-    // One column: by one-wave tiles, on the context's copy of A in fragment order
-    // or on one made here (n = 10^4, B = 1024 int8, 300 iterations: 27.5 -> 6.8 ms).
-    const char* env = std::getenv("PDBO_FRAG");
-    const int64_t rb = c->kind == 0 ? (int64_t)ld * element_bytes(c->prec) : 0;
-    if (c->kind == 0 && !(env && *env && std::atoi(env) <= 0)) {
-      if (c->frag >= 0) {
-        c->cert_af = c->insts_h[0].Af;
-      } else if ((double)n * rb <= (double)kFragBytes) {
-        uint8_t* af = nullptr;
-        if (dalloc(c, &af, (size_t)roundup(n, 16) * rb) == PDBO_OK) {
-          HIPCHK(c, launch_frag_pack(c->insts_h[0].A, n, rb, !dense_cfg(c->cfg).dma, af, c->stream));
-          c->cert_af = af;
-        } else {
-          c->err.clear();  // no room for the copy: the context's tiles
-        }
-      }
+  auto need = [&](auto** p, size_t count) { return *p ? PDBO_OK : dalloc(c, p, count); };
+  STCHK(need(&c->cert_x, 2 * (size_t)ld));
+  STCHK(need(&c->cert_y, (size_t)ld));
+  STCHK(need(&c->cert_xs, 2 * (size_t)ld * 4));
+  STCHK(need(&c->cert_xr, (size_t)ld));
+  STCHK(need(&c->cert_rows, 4 * (size_t)n));
+  STCHK(need(&c->cert_res, 4));
+  STCHK(need(&c->cert_i64, 4 + 2 * (size_t)std::max(1, 2048)));
+  STCHK(need(&c->cert_u64, 1));
+  STCHK(need(&c->cert_bx, (size_t)n));
+  // One column: by one-wave tiles, on the context's copy of A in fragment order
+  // or on one made here (n = 10^4, B = 1024 int8, 300 iterations: 27.5 -> 6.8 ms);
+  // without room for it on the context's tiles, which add in the same order.
+  const char* env = std::getenv("PDBO_FRAG");
+  const int64_t rb = c->kind == 0 ? (int64_t)ld * element_bytes(c->prec) : 0;
+  if (c->kind == 0 && !c->cert_frag && !(env && *env && std::atoi(env) <= 0) &&
+      (c->frag >= 0 || (double)n * rb <= (double)kFragBytes)) {
+    pdbo_status st = PDBO_OK;
+    if (c->frag >= 0) {
+      c->cert_af = c->insts_h[0].Af;
+    } else if (!c->cert_af) {
+      uint8_t* af = nullptr;
+      st = dalloc(c, &af, (size_t)roundup(n, 16) * rb);
+      if (st == PDBO_OK)
+        HIPCHK(c, launch_frag_pack(c->insts_h[0].A, n, rb, !dense_cfg(c->cfg).dma, af, c->stream));
+      c->cert_af = af;
     }
-    if (c->cert_af) {
-      STCHK(dalloc(c, &c->cert_xf, 2 * 16 * (size_t)rb));
-      STCHK(dalloc(c, &c->cert_tiles, (size_t)(n + 15) / 16));
+    if (st == PDBO_OK) st = need(&c->cert_xf, 2 * 16 * (size_t)rb);
+    if (st == PDBO_OK) st = need(&c->cert_tiles, (size_t)(n + 15) / 16);
+    if (st == PDBO_OK) {
       std::vector<TileDev> tiles;
       for (int m = 0; m < (n + 15) / 16; ++m) tiles.push_back(TileDev{0, 16 * m, 0, m});
       HIPCHK(c, hipMemcpy(c->cert_tiles, tiles.data(), tiles.size() * sizeof(TileDev),
                           hipMemcpyHostToDevice));
+      c->cert_frag = true;
+    } else if (st == PDBO_ENOMEM) {
+      c->err.clear();
+    } else {
+      return st;
     }
-    STCHK(dalloc(c, &c->cert_xr, (size_t)ld));
-    STCHK(dalloc(c, &c->cert_rows, 4 * (size_t)n));
-    STCHK(dalloc(c, &c->cert_res, 4));
-    STCHK(dalloc(c, &c->cert_i64, 4 + 2 * (size_t)std::max(1, 2048)));
-    STCHK(dalloc(c, &c->cert_u64, 1));
-    STCHK(dalloc(c, &c->cert_bx, (size_t)n));
   }
   if (c->kind == 0 && !c->scratch_inst_d) STCHK(dalloc(c, &c->scratch_inst_d, 1));
   float* x0 = c->cert_x;
@@ -3288,7 +3296,7 @@ pdbo_status qubo_dual_bound(pdbo_ctx* c, double ybar, int32_t iters, double* low
       HIPCHK(c, launch_set_state(x0, nullptr, 1, n, ld, x0, nullptr, I.Xs[0], c->prec, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->scratch_inst_d, &I, sizeof(I), hipMemcpyHostToDevice, c->stream));
     int parity = 0;
-    const bool fr = c->cert_af != nullptr;
+    const bool fr = c->cert_frag;
     const int staged = !dense_cfg(c->cfg).dma;
     if (fr) HIPCHK(c, launch_frag_pack(I.Xs[0], 1, (int64_t)ld * EB, staged, I.Xf[0], c->stream));
     for (int t = 0; t < iters; ++t) {

@@ -87,3 +87,46 @@ def test_csr_maxcut_and_mis(tile):
         assert r["lower_bound"] <= best
         say(f"   incumbent {best}, lower bound {r['lower_bound']:.2f}")
         ctx.destroy()
+
+
+@pytest.mark.parametrize("kind", ["dense", "csr", "rows"])
+def test_allocation_failures(kind, monkeypatch):
+    """A failing allocation gives ENOMEM or, where only the copy in fragment order
+    is concerned, the same bound from the context's tiles; the call after it is
+    complete again."""
+    P = require_gpu()
+    if kind == "dense":
+        q = W.random_dense_qubo(300, -50, 50, W.rng_for(3, 53, 0, 300))
+        mk = lambda: P.qubo_gda_init(q, W.gda_params("qubo", B=40, T=1, scale=200.0, precision="i8", tile=2), None)
+    else:
+        q = W.maxcut_c2(1, n=301, M=900)
+        tile = 1 if kind == "csr" else 2
+        mk = lambda: P.qubo_gda_init(q, W.gda_params("maxcut", B=5, T=1, tile=tile), None)
+
+    def bound(ctx):
+        r = P.qubo_dual_bound(ctx, 30)
+        return [r[k] for k in sorted(r)]
+
+    ctx = mk()
+    ref = bound(ctx)
+    ctx.destroy()
+    refused = fell_back = 0
+    for k in range(1, 16):
+        say(f"[dual enomem] {kind} allocation {k}")
+        ctx = mk()
+        monkeypatch.setenv("PDBO_FAIL_ALLOC_AT", "0")
+        P.qubo_gda_init(q, W.gda_params("maxcut", B=1, T=1, tile=2), None).destroy()  # counts from the change below
+        monkeypatch.setenv("PDBO_FAIL_ALLOC_AT", str(k))
+        try:
+            got = bound(ctx)
+            fell_back += 1
+        except P.PdboError as e:
+            assert e.status == 2
+            refused += 1
+            got = ref
+        again = bound(ctx)
+        monkeypatch.setenv("PDBO_FAIL_ALLOC_AT", "0")
+        for a, b, c in zip(got, again, ref):
+            assert np.array_equal(a, c) and np.array_equal(b, c)
+        ctx.destroy()
+    assert refused >= 9 and fell_back >= 3
