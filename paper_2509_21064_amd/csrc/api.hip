@@ -1052,6 +1052,20 @@ pdbo_status setup_frags(pdbo_ctx* c) {
   return frag_shadow(c);
 }
 
+// Back to the workgroup tiles; `mark`: the context's allocations before setup_frags.
+void drop_frags(pdbo_ctx* c, size_t mark) {
+  (void)hipStreamSynchronize(c->stream);
+  for (size_t k = mark; k < c->allocs.size(); ++k) (void)hipFree(c->allocs[k]);
+  c->allocs.resize(mark);
+  for (InstDev& I : c->insts_h) {
+    I.Af = nullptr;
+    I.Xf[0] = I.Xf[1] = nullptr;
+  }
+  c->frag_tiles_d = nullptr;
+  c->frag = -1;
+  c->err.clear();
+}
+
 pdbo_status upload_dense_tables(pdbo_ctx* c) {
   build_tiles(c);
   std::vector<int2> work;  // alive until the stream is synchronised below
@@ -1920,7 +1934,14 @@ static pdbo_status dense_init(int k, const pdbo_qubo* probs, const pdbo_params* 
     // PDBO_FRAG=0 keeps the tiles, 1 .. dense_num_frags() takes that width
     const char* e = std::getenv("PDBO_FRAG");
     c->frag = e && *e ? std::min(std::atoi(e), dense_num_frags()) - 1 : frag_choice(c);
-    if (c->frag >= 0) st = setup_frags(c);
+    if (c->frag >= 0) {
+      const size_t mark = c->allocs.size();
+      st = setup_frags(c);
+      if (st == PDBO_ENOMEM) {  // no room for the copies: the tiles, same bits
+        drop_frags(c, mark);
+        st = PDBO_OK;
+      }
+    }
   }
   if (st == PDBO_OK) st = upload_dense_tables(c);
   if (st != PDBO_OK) {

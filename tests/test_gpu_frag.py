@@ -120,3 +120,40 @@ def test_dual_of_tiled_contexts(tile, prec, monkeypatch):
         ctx.destroy()
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+def test_no_room_for_the_copies(monkeypatch):
+    """The operands in fragment order are optional: an allocation of theirs that
+    fails leaves the context on its tiles, with the same run, and frees the rest."""
+    import torch
+    P = require_gpu()
+    q = W.random_dense_qubo(900, -60, 60, W.rng_for(5, 1, 0, 900))
+    par = W.gda_params("qubo", B=20, T=1, scale=600.0, precision="i8", seed=3)
+
+    def run():
+        ctx = P.qubo_gda_init(q, par, None)
+        name = ctx.tile_name
+        ctx.step(70)
+        out = [ctx.objectives(), *ctx.get_state(), ctx.result()["best_x"]]
+        ctx.destroy()
+        return name, out
+
+    ref_name, ref = run()
+    assert ref_name.startswith("frag")
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    refused = fell_back = 0
+    for k in range(1, 40):
+        say(f"[frag enomem] allocation {k}")
+        monkeypatch.setenv("PDBO_FAIL_ALLOC_AT", str(k))
+        try:
+            name, got = run()
+            fell_back += not name.startswith("frag")
+            for a, b in zip(got, ref):
+                assert np.array_equal(a, b)
+        except P.PdboError as e:
+            assert e.status == 2
+            refused += 1
+        monkeypatch.setenv("PDBO_FAIL_ALLOC_AT", "0")
+        assert torch.cuda.mem_get_info()[0] >= free0 - (2 << 20), k
+    assert fell_back == 4 and refused >= 5  # A, the two shadows and the tile table
