@@ -335,9 +335,16 @@ static hipError_t launch_kr(const KcutDev& d, int nsteps, hipStream_t s) {
   return hipGetLastError();
 }
 
+// A launch's records fit kResTrace.  Restarts beyond the first kKrTogether wait
+// for a CU within a launch, so launches are then short: the times of
+// improvements tell when they were made to within one (n = 10^4, k = 3, B = 300:
+// 2 ms).
+constexpr int kKrTogether = 256, kKrSteps = 64;
+
 hipError_t launch_kcut_resident(const KcutDev& d, int nsteps, hipStream_t s) {
-  for (int done = 0; done < nsteps;) {  // a launch's records fit kResTrace
-    const int k = nsteps - done < kResTrace - 1 ? nsteps - done : kResTrace - 1;
+  const int most = d.B > kKrTogether ? kKrSteps : kResTrace - 1;
+  for (int done = 0; done < nsteps;) {
+    const int k = nsteps - done < most ? nsteps - done : most;
     hipError_t e = hipErrorInvalidValue;
     switch (d.k) {
       case 2: e = launch_kr<2>(d, k, s); break;

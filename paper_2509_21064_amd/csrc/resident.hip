@@ -481,6 +481,9 @@ static hipError_t launch_res(const CsrDev& d, int64_t t0, int nsteps, hipStream_
 // the records the restarts kept (at most one per restart and iteration of the
 // launch) hold them all: at each iteration the least (F, b) of its records is
 // an improvement when F is below the incumbent and every earlier iteration's.
+// The restarts run free of each other, so the time of an improvement is the
+// latest of those up to its iteration: the incumbent of iteration t is known
+// when every improvement up to t has been made, and times increase with t.
 constexpr int kMergeThreads = 1024;
 
 __global__ void __launch_bounds__(kMergeThreads)
@@ -493,6 +496,7 @@ __global__ void __launch_bounds__(kMergeThreads)
   __shared__ long long sF[kResTrace];
   __shared__ int sb[kResTrace];
   __shared__ int spos[kResTrace];
+  __shared__ unsigned long long sts[kResTrace];  // times of the improvements, 0 elsewhere
   __shared__ long long wmin[NW];
   __shared__ int wcnt[NW];
   __shared__ int last;
@@ -503,6 +507,7 @@ __global__ void __launch_bounds__(kMergeThreads)
   for (int u = tid; u < kResTrace; u += kMergeThreads) {
     sF[u] = LLONG_MAX;
     sb[u] = INT_MAX;
+    sts[u] = 0;
   }
   if (tid == 0) last = -1;
   __syncthreads();
@@ -546,16 +551,30 @@ __global__ void __launch_bounds__(kMergeThreads)
   __syncthreads();
   const int lu = last;
   records([&](const TraceRec& q, int b, int u) {
-    if (spos[u] < 0 || b != sb[u] || q.F != sF[u]) return;
-    const int at = len0 + spos[u];
+    if (spos[u] >= 0 && b == sb[u] && q.F == sF[u]) sts[u] = q.ts;
+  });
+  __syncthreads();
+  // inclusive running maximum of the times
+  uint64_t ts = sts[tid];
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint64_t v = __shfl_up(ts, o);
+    if (lane >= o && v > ts) ts = v;
+  }
+  if (lane == 63) wmin[wid] = (long long)ts;
+  __syncthreads();
+  for (int w = 0; w < wid; ++w) ts = ts > (uint64_t)wmin[w] ? ts : (uint64_t)wmin[w];
+  if (imp) {
+    const TraceRec q{t0 + tid, F, (int64_t)sb[tid], ts};
+    const int at = len0 + pos;
     if (at < trace_cap) {
       trace[at] = q;
-      if (u == lu || at == trace_cap - 1) *trace_len = at + 1;
-    } else if (u == lu) {
+      if (tid == lu || at == trace_cap - 1) *trace_len = at + 1;
+    } else if (tid == lu) {
       *trace_len = trace_cap;
     }
-    if (u == lu) *inc = Incumbent{q.F, q.t, (int64_t)b, q.ts};
-  });
+    if (tid == lu) *inc = Incumbent{q.F, q.t, q.b, q.ts};
+  }
   if (lu >= 0) {
     // the winner's last improvement is its least objective, which is the
     // incumbent's: its kept vector is the incumbent's

@@ -72,3 +72,26 @@ def test_long_call_set_state_and_restart(monkeypatch):
         out.append(got)
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("B", [7, 600])
+def test_times_of_improvements(B, monkeypatch):
+    """More restarts than run at once: the improvements' times do not fall as t
+    grows, the result's is the last one's, and the records are the row-parallel
+    kernels'."""
+    P = require_gpu()
+    g = W.kcut_graph(2000, 4000, 3, rep=7)
+    out = []
+    for res in ("1", "0"):
+        say(f"[kcut times] B={B} resident={res}")
+        monkeypatch.setenv("PDBO_KCUT_RESIDENT", res)
+        ctx = P.kcut_gda_init(g, _params(B, "quad", 0.01), None)
+        for t in (150, 50):
+            ctx.step(t)
+        tr, r = ctx.trace(), ctx.result()
+        ctx.destroy()
+        assert len(tr["t"]) > 20 and (np.diff(tr["t"]) > 0).all()
+        assert (np.diff(tr["sec"]) >= 0).all() and tr["sec"][0] >= 0 and r["time_to_best_s"] == tr["sec"][-1]
+        out.append((tr["t"], tr["F"], tr["b"], r["best_obj"], r["best_x"]))
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
