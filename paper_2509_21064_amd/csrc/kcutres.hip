@@ -336,10 +336,11 @@ static hipError_t launch_kr(const KcutDev& d, int nsteps, hipStream_t s) {
 }
 
 // A launch's records fit kResTrace.  Restarts beyond the first kKrTogether wait
-// for a CU within a launch, so launches are then short: the times of
+// for a CU within a launch, so launches are then short and the times of
 // improvements tell when they were made to within one (n = 10^4, k = 3, B = 300:
-// 2 ms).
-constexpr int kKrTogether = 256, kKrSteps = 64;
+// 8 ms; 64 iterations a launch cost n = 1000, B = 1024 15%: 10.2 -> 11.7 us an
+// iteration).
+constexpr int kKrTogether = 256, kKrSteps = 256;
 
 hipError_t launch_kcut_resident(const KcutDev& d, int nsteps, hipStream_t s) {
   const int most = d.B > kKrTogether ? kKrSteps : kResTrace - 1;

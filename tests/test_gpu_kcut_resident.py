@@ -86,7 +86,7 @@ def test_times_of_improvements(B, monkeypatch):
         say(f"[kcut times] B={B} resident={res}")
         monkeypatch.setenv("PDBO_KCUT_RESIDENT", res)
         ctx = P.kcut_gda_init(g, _params(B, "quad", 0.01), None)
-        for t in (150, 50):
+        for t in (150, 50, 300):
             ctx.step(t)
         tr, r = ctx.trace(), ctx.result()
         ctx.destroy()
