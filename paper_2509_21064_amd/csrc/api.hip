@@ -197,6 +197,16 @@ pdbo_status hipfail(pdbo_ctx* c, const char* what, hipError_t e) {
     if (s_ != PDBO_OK) return s_;       \
   } while (0)
 
+// f(), with host memory that ran out as PDBO_ENOMEM: no exception leaves the library
+template <typename F>
+pdbo_status guarded(pdbo_ctx* c, F f) {
+  try {
+    return f();
+  } catch (...) {
+    return fail(c, PDBO_ENOMEM, "host allocation failed");
+  }
+}
+
 template <typename T>
 pdbo_status dalloc(pdbo_ctx* c, T** p, size_t count) {
   *p = nullptr;
@@ -3802,7 +3812,7 @@ pdbo_status maxsat_gda_init(const pdbo_maxsat* prob, const pdbo_params* p, void*
     // satres.hip takes the formula when its table fits in LDS and the weights
     // are exact in float16 (PDBO_SAT_RESIDENT=0 keeps the general kernels)
     const char* res_env = std::getenv("PDBO_SAT_RESIDENT");
-    const bool res = satres_copies(n, k) > 0 && wmax <= 2048 && !(res_env && std::atoi(res_env) == 0);
+    bool res = satres_copies(n, k) > 0 && wmax <= 2048 && !(res_env && std::atoi(res_env) == 0);
     int32_t *dl = nullptr, *dw = nullptr;
     STCHK(dalloc(c, &dl, codes.size()));
     STCHK(dalloc(c, &dw, m));
@@ -3828,6 +3838,22 @@ pdbo_status maxsat_gda_init(const pdbo_maxsat* prob, const pdbo_params* p, void*
     HIPCHK(c, hipMemcpyAsync(dpp, pptr.data(), (size_t)(n + 1) * 4, hipMemcpyHostToDevice, c->stream));
     d.order = dord;
     d.pinc_ptr = dpp;
+    uint32_t* de = nullptr;
+    if (res) {
+      // a layout too large for its 32-bit offsets (a variable of some 10^7
+      // occurrences pads its slice of 64 to as many), the host or the device
+      // leaves the general kernels
+      const std::string err0 = g_last_error;
+      pdbo_status ls = guarded(c, [&] { return sat_layout(n, m, k, ptr, inc, codes, ord, posv, sl); });
+      if (ls == PDBO_OK) ls = dalloc(c, &de, sl.ent.size());
+      if (ls != PDBO_OK && ls != PDBO_ERANGE && ls != PDBO_ENOMEM) return ls;
+      res = ls == PDBO_OK;
+      if (!res) {
+        sl = SatLayout();
+        c->err.clear();
+        g_last_error = err0;
+      }
+    }
     if (!res) {
       // variable-major lists, and by position with the other literals' codes
       // renamed to positions
@@ -3854,12 +3880,9 @@ pdbo_status maxsat_gda_init(const pdbo_maxsat* prob, const pdbo_params* p, void*
       d.pinc = dpi;
     }
     if (res) {
-      STCHK(sat_layout(n, m, k, ptr, inc, codes, ord, posv, sl));
-      uint32_t* de = nullptr;
       int2* ds = nullptr;
       uint16_t* dli = nullptr;
       int32_t* dpos = nullptr;
-      STCHK(dalloc(c, &de, sl.ent.size()));
       STCHK(dalloc(c, &ds, sl.slice.size()));
       STCHK(dalloc(c, &dli, sl.lit.size()));
       STCHK(dalloc(c, &dpos, n));

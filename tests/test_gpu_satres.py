@@ -121,3 +121,35 @@ def test_lagrangian_outside_the_box_matches_general_kernels(n, m, k, wmax, monke
             occ = np.bincount(np.abs(f.lits).ravel() - 1, minlength=n).max()
             tol = 2.0 * (occ * wmax * 1.2 ** (k - 1) / 2.0 + 3.0) * (occ + k + 4) * 2.0 ** -24
             assert np.abs(out[0][1][:2] - X.grad.numpy()).max() <= tol
+
+
+def test_no_room_for_the_layout(monkeypatch):
+    """Without room for the layout on literals a formula runs on the general
+    kernels, with the same bits."""
+    P = require_gpu()
+    f = _formula(700, 4.2, 3, 10)
+    p = W.gda_params("maxsat", B=3, T=1, scale=5.0, seed=2)
+
+    def run():
+        ctx = P.maxsat_gda_init(f, p, None)
+        ctx.step(40)
+        out = [*ctx.get_state(), ctx.objectives(), ctx.result()["best_x"]]
+        ctx.destroy()
+        return out
+
+    monkeypatch.setenv("PDBO_SAT_RESIDENT", "0")
+    ref = run()
+    monkeypatch.setenv("PDBO_SAT_RESIDENT", "1")
+    refused = []
+    for k in range(1, 25):
+        say(f"[satres enomem] allocation {k}")
+        monkeypatch.setenv("PDBO_FAIL_ALLOC_AT", str(k))
+        try:
+            for a, b in zip(run(), ref):
+                assert np.array_equal(a, b)
+        except P.PdboError as e:
+            assert e.status == 2
+            refused.append(k)
+        monkeypatch.setenv("PDBO_FAIL_ALLOC_AT", "0")
+    last = max(refused)
+    assert len(refused) == last - 1  # one of them is the layout's
