@@ -66,7 +66,8 @@ bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 
 // Fault injection for tests: PDBO_FAIL_ALLOC_AT=k makes the k-th device
 // allocation after the variable last changed value fail with PDBO_ENOMEM
-// (0 or unset: none fails).
+// (0 or unset: none fails); with PDBO_FAIL_ALLOC_HOST set, an allocation of host
+// memory fails there instead.
 std::mutex g_alloc_mu;
 long g_alloc_count = 0;
 std::string g_alloc_env;
@@ -211,7 +212,10 @@ template <typename T>
 pdbo_status dalloc(pdbo_ctx* c, T** p, size_t count) {
   *p = nullptr;
   size_t bytes = std::max<size_t>(count * sizeof(T), 16);
-  if (inject_alloc_failure()) bytes = size_t(1) << 50;  // more than any device has
+  if (inject_alloc_failure()) {
+    if (std::getenv("PDBO_FAIL_ALLOC_HOST")) throw std::bad_alloc();
+    bytes = size_t(1) << 50;  // more than any device has
+  }
   void* q = nullptr;
   hipError_t e = hipMalloc(&q, bytes);
   if (e != hipSuccess) return hipfail(c, "hipMalloc", e);
@@ -1922,23 +1926,24 @@ static pdbo_status dense_init(int k, const pdbo_qubo* probs, const pdbo_params* 
   c->insts_h.resize(k);
   // The first instance is canonicalised (host only) before any HIP call, so
   // that its range errors come back on any machine.
-  pdbo_status st = PDBO_OK;
-  for (int i = 0; i < k && st == PDBO_OK; ++i) {
-    DenseCanon C;
-    st = canon_dense(&probs[i], C);
-    if (st == PDBO_OK && pars[i].precision == PDBO_I8 && C.amax > 127)
-      st = fail(nullptr, PDBO_EUNSUPPORTED, "the INT8 operand form needs |Ahat_ij| <= 127");
-    if (st == PDBO_OK && i == 0) st = begin_ctx(c, stream, &pars[0]);
-    if (st == PDBO_OK) st = setup_dense_instance(c, C, &pars[i], c->insts_h[i]);
+  auto instance = [&](int i) -> pdbo_status {
     c->n_of.push_back(probs[i].n);
-  }
+    DenseCanon C;
+    STCHK(canon_dense(&probs[i], C));
+    if (pars[i].precision == PDBO_I8 && C.amax > 127)
+      return fail(nullptr, PDBO_EUNSUPPORTED, "the INT8 operand form needs |Ahat_ij| <= 127");
+    if (i == 0) STCHK(begin_ctx(c, stream, &pars[0]));
+    return setup_dense_instance(c, C, &pars[i], c->insts_h[i]);
+  };
+  pdbo_status st = PDBO_OK;
+  for (int i = 0; i < k && st == PDBO_OK; ++i) st = guarded(c, [&] { return instance(i); });
   if (st == PDBO_OK && pars[0].tile == 0) {
     // autotune large problems (or when asked); PDBO_AUTOTUNE=0 keeps the heuristic
     const char* e = std::getenv("PDBO_AUTOTUNE");
     double work = 0;
     for (const InstDev& I : c->insts_h) work += (double)I.n * I.n * I.B;
     const bool want = e ? std::atoi(e) != 0 : work >= (double)(1 << 30);
-    if (want) st = autotune_dense(c);
+    if (want) st = guarded(c, [&] { return autotune_dense(c); });
   }
   if (st == PDBO_OK && pars[0].tile == 0) {
     // PDBO_FRAG=0 keeps the tiles, 1 .. dense_num_frags() takes that width
@@ -1946,14 +1951,14 @@ static pdbo_status dense_init(int k, const pdbo_qubo* probs, const pdbo_params* 
     c->frag = e && *e ? std::min(std::atoi(e), dense_num_frags()) - 1 : frag_choice(c);
     if (c->frag >= 0) {
       const size_t mark = c->allocs.size();
-      st = setup_frags(c);
+      st = guarded(c, [&] { return setup_frags(c); });
       if (st == PDBO_ENOMEM) {  // no room for the copies: the tiles, same bits
         drop_frags(c, mark);
         st = PDBO_OK;
       }
     }
   }
-  if (st == PDBO_OK) st = upload_dense_tables(c);
+  if (st == PDBO_OK) st = guarded(c, [&] { return upload_dense_tables(c); });
   if (st != PDBO_OK) {
     const std::string msg = c->err.empty() ? g_last_error : c->err;
     pdbo_destroy(c);
@@ -1987,7 +1992,7 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
     return fail(nullptr, PDBO_EINVAL, "CSR instances take tile 0 (automatic), 1 (restart-resident) "
                                       "or 2 (row-parallel)");
   CsrCanon C;
-  STCHK(canon_csr(q, C));
+  STCHK(guarded(nullptr, [&] { return canon_csr(q, C); }));
   const int n = q->n;
   const bool compact = n <= 65536 && C.amax <= 32767;  // packed 16-bit column / 16-bit value
   const bool fits = csr_fits(n, (int64_t)C.col.size(), compact, nullptr);
@@ -1998,7 +2003,11 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
   const int64_t lim32 = int64_t(1) << 31;
   const bool small32 = 512 * C.rowabs < lim32 && 512 * cmax < lim32;
   const bool tot32 = small32 && (int64_t)n * C.rowabs < lim32 && (int64_t)n * cmax < lim32;
-  const std::vector<int32_t> order = degree_order(n, C.rp.data());
+  std::vector<int32_t> order;
+  STCHK(guarded(nullptr, [&] {
+    order = degree_order(n, C.rp.data());
+    return PDBO_OK;
+  }));
   // resident.hip: weights exact in float16, twice a row's sum exact in float32,
   // totals in int32, positions within a 16-bit byte offset
   const bool res_ok = C.amax <= 2048 && C.rowabs < (1 << 23) && tot32 && csr_resident_rows(n) > 0 &&
@@ -2030,7 +2039,7 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
   c->kind = 1;
   c->compact = compact;
   c->n_of.push_back(n);
-  pdbo_status st = begin_ctx(c, stream, p);
+  pdbo_status st = guarded(c, [&] { return begin_ctx(c, stream, p); });
   auto run = [&]() -> pdbo_status {
     const int B = p->B, ld = roundup(n, kLdAlign);
     const int64_t nnz = (int64_t)C.col.size();
@@ -2194,7 +2203,7 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return PDBO_OK;
   };
-  if (st == PDBO_OK) st = run();
+  if (st == PDBO_OK) st = guarded(c, run);
   if (st != PDBO_OK) {
     const std::string msg = c->err.empty() ? g_last_error : c->err;
     pdbo_destroy(c);
@@ -2216,7 +2225,7 @@ static pdbo_status spmm_init(const CsrCanon* C, const RealCanon* R, const pdbo_p
   pdbo_ctx* c = new pdbo_ctx();
   c->kind = 3;
   c->n_of.push_back(n);
-  pdbo_status st = begin_ctx(c, stream, p);
+  pdbo_status st = guarded(c, [&] { return begin_ctx(c, stream, p); });
   auto run = [&]() -> pdbo_status {
     const std::vector<int32_t>& hrp = C ? C->rp : R->rp;
     const std::vector<int32_t>& hcol = C ? C->col : R->col;
@@ -2360,7 +2369,7 @@ static pdbo_status spmm_init(const CsrCanon* C, const RealCanon* R, const pdbo_p
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return PDBO_OK;
   };
-  if (st == PDBO_OK) st = run();
+  if (st == PDBO_OK) st = guarded(c, run);
   if (st != PDBO_OK) {
     const std::string msg = c->err.empty() ? g_last_error : c->err;
     pdbo_destroy(c);
@@ -2379,7 +2388,7 @@ static pdbo_status real_init(const pdbo_qubo* q, const pdbo_params* p, void* str
     return fail(nullptr, PDBO_EUNSUPPORTED, "float64 weights run on the row-parallel CSR path "
                                             "(tile 0 or 2)");
   RealCanon R;
-  STCHK(canon_real(q, p->scale, R));
+  STCHK(guarded(nullptr, [&] { return canon_real(q, p->scale, R); }));
   return spmm_init(nullptr, &R, p, stream, out);
 }
 
@@ -2596,11 +2605,18 @@ pdbo_status qubo_gda_init(const pdbo_qubo* prob, const pdbo_params* par, void* s
   const int cached = autotune_lookup(key);
   if (cached == 0) return init_as_given(prob, par, stream, out);
   HostQubo h;
-  if (prob->format == PDBO_DENSE)
-    host_to_csr(prob, h);
-  else
-    host_to_dense(prob, h);
   const std::string err0 = g_last_error;  // a refusal of the other path is no error of the call
+  const pdbo_status hs = guarded(nullptr, [&] {
+    if (prob->format == PDBO_DENSE)
+      host_to_csr(prob, h);
+    else
+      host_to_dense(prob, h);
+    return PDBO_OK;
+  });
+  if (hs != PDBO_OK) {
+    g_last_error = err0;
+    return init_as_given(prob, par, stream, out);
+  }
   if (cached == 1) {
     if (init_as_given(&h.q, par, stream, out) == PDBO_OK) return PDBO_OK;
     g_last_error = err0;
@@ -3507,7 +3523,7 @@ pdbo_status kcut_gda_init(const pdbo_kcut* g, const pdbo_params* p, void* stream
   pdbo_ctx* c = new pdbo_ctx();
   c->kind = 4;
   c->n_of.push_back(n);
-  pdbo_status st = begin_ctx(c, stream, p);
+  pdbo_status st = guarded(c, [&] { return begin_ctx(c, stream, p); });
   auto run = [&]() -> pdbo_status {
     KcutDev& d = c->kcut;
     std::memset(&d, 0, sizeof(d));
@@ -3601,7 +3617,7 @@ pdbo_status kcut_gda_init(const pdbo_kcut* g, const pdbo_params* p, void* stream
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return PDBO_OK;
   };
-  if (st == PDBO_OK) st = run();
+  if (st == PDBO_OK) st = guarded(c, run);
   if (st != PDBO_OK) {
     const std::string msg = c->err.empty() ? g_last_error : c->err;
     pdbo_destroy(c);
@@ -3746,47 +3762,53 @@ pdbo_status maxsat_gda_init(const pdbo_maxsat* prob, const pdbo_params* p, void*
   if (!sat_fits(n, nullptr))
     return fail(nullptr, PDBO_EUNSUPPORTED, "n too large for the restart-resident MaxSAT kernel");
   // literal codes and the variable-major occurrence lists
-  std::vector<int32_t> codes((size_t)m * k), wv(m);
-  std::vector<int32_t> ptr(n + 1, 0);
-  for (int j = 0; j < m; ++j) {
-    wv[j] = prob->w ? prob->w[j] : 1;
-    for (int l = 0; l < k; ++l) {
-      const int32_t v = prob->lits[(size_t)j * k + l];
-      const int32_t var = (v < 0 ? -v : v) - 1;
-      codes[(size_t)j * k + l] = (int32_t)((uint32_t)var | (v < 0 ? 0x80000000u : 0u));
-      ptr[var + 1]++;
-    }
-  }
-  for (int i = 0; i < n; ++i) ptr[i + 1] += ptr[i];
-  // Every clause is counted in the exact evaluation by one of its variables,
-  // its owner: the variable with the fewest clauses owned so far when the
-  // clause comes up, so that each variable owns about m/n of them (the
-  // evaluation work of the threads stays even).
-  std::vector<int32_t> owner(m);
-  {
-    std::vector<int32_t> owned(n, 0);
+  std::vector<int32_t> codes, wv, ptr, inc;
+  auto lists = [&]() -> pdbo_status {
+    codes.resize((size_t)m * k);
+    wv.resize(m);
+    ptr.assign(n + 1, 0);
     for (int j = 0; j < m; ++j) {
-      int best = 0;
-      for (int l = 1; l < k; ++l)
-        if (owned[codes[(size_t)j * k + l] & 0x7fffffff] < owned[codes[(size_t)j * k + best] & 0x7fffffff])
-          best = l;
-      owner[j] = best;
-      owned[codes[(size_t)j * k + best] & 0x7fffffff]++;
+      wv[j] = prob->w ? prob->w[j] : 1;
+      for (int l = 0; l < k; ++l) {
+        const int32_t v = prob->lits[(size_t)j * k + l];
+        const int32_t var = (v < 0 ? -v : v) - 1;
+        codes[(size_t)j * k + l] = (int32_t)((uint32_t)var | (v < 0 ? 0x80000000u : 0u));
+        ptr[var + 1]++;
+      }
     }
-  }
-  std::vector<int32_t> inc((size_t)ptr[n] * k);
-  std::vector<int32_t> fillp(ptr.begin(), ptr.end() - 1);
-  for (int j = 0; j < m; ++j)
-    for (int l = 0; l < k; ++l) {
-      const int32_t code = codes[(size_t)j * k + l];
-      const int var = code & 0x7fffffff;
-      const int e = fillp[var]++;
-      int o = 0;
-      for (int l2 = 0; l2 < k; ++l2)
-        if (l2 != l) inc[(size_t)e * k + o++] = codes[(size_t)j * k + l2];
-      const int32_t meta = wv[j] | ((code < 0 ? 1 : 0) << 30) | ((l == owner[j] ? 1 : 0) << 29);
-      inc[(size_t)e * k + (k - 1)] = meta;
+    for (int i = 0; i < n; ++i) ptr[i + 1] += ptr[i];
+    // Every clause is counted in the exact evaluation by one of its variables,
+    // its owner: the variable with the fewest clauses owned so far when the
+    // clause comes up, so that each variable owns about m/n of them (the
+    // evaluation work of the threads stays even).
+    std::vector<int32_t> owner(m);
+    {
+      std::vector<int32_t> owned(n, 0);
+      for (int j = 0; j < m; ++j) {
+        int best = 0;
+        for (int l = 1; l < k; ++l)
+          if (owned[codes[(size_t)j * k + l] & 0x7fffffff] < owned[codes[(size_t)j * k + best] & 0x7fffffff])
+            best = l;
+        owner[j] = best;
+        owned[codes[(size_t)j * k + best] & 0x7fffffff]++;
+      }
     }
+    inc.resize((size_t)ptr[n] * k);
+    std::vector<int32_t> fillp(ptr.begin(), ptr.end() - 1);
+    for (int j = 0; j < m; ++j)
+      for (int l = 0; l < k; ++l) {
+        const int32_t code = codes[(size_t)j * k + l];
+        const int var = code & 0x7fffffff;
+        const int e = fillp[var]++;
+        int o = 0;
+        for (int l2 = 0; l2 < k; ++l2)
+          if (l2 != l) inc[(size_t)e * k + o++] = codes[(size_t)j * k + l2];
+        const int32_t meta = wv[j] | ((code < 0 ? 1 : 0) << 30) | ((l == owner[j] ? 1 : 0) << 29);
+        inc[(size_t)e * k + (k - 1)] = meta;
+      }
+    return PDBO_OK;
+  };
+  STCHK(guarded(nullptr, lists));
 
   std::vector<uint64_t> pinc3;  // host staging, alive until init syncs
   std::vector<int32_t> slice;
@@ -3795,7 +3817,7 @@ pdbo_status maxsat_gda_init(const pdbo_maxsat* prob, const pdbo_params* p, void*
   pdbo_ctx* c = new pdbo_ctx();
   c->kind = 2;
   c->n_of.push_back(n);
-  pdbo_status st = begin_ctx(c, stream, p);
+  pdbo_status st = guarded(c, [&] { return begin_ctx(c, stream, p); });
   auto run = [&]() -> pdbo_status {
     const int B = p->B, ld = roundup(n, kLdAlign);
     SatDev& d = c->sat;
@@ -3956,7 +3978,7 @@ pdbo_status maxsat_gda_init(const pdbo_maxsat* prob, const pdbo_params* p, void*
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return PDBO_OK;
   };
-  if (st == PDBO_OK) st = run();
+  if (st == PDBO_OK) st = guarded(c, run);
   if (st != PDBO_OK) {
     const std::string msg = c->err.empty() ? g_last_error : c->err;
     pdbo_destroy(c);
