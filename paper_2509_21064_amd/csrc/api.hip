@@ -1656,6 +1656,14 @@ bool host_parallel(int count, int grain, F f) {
   return ok;
 }
 
+// f over shares of the `count` slices or segments of a layout of `entries`
+// entries, each worth a thread from some 0.1 ms on
+template <typename F>
+void layout_parallel(int count, int64_t entries, F f) {
+  const int64_t shares = std::max<int64_t>(1, entries / 8192);
+  if (!host_parallel(count, (int)std::max<int64_t>(1, count / shares), f)) throw std::bad_alloc();
+}
+
 // The layout of the resident kernels (CsrDev::rent, KcutDev::rent): entries of
 // the rows order[q] by slices of 64 positions q; a row's full groups of four
 // entries, then one group with what is left of it (one to three), each row's
@@ -1685,12 +1693,14 @@ int64_t res_layout_words(int n, const int32_t* rp, const std::vector<int32_t>& o
 }
 
 // rows by decreasing degree (ties by index): a wave's rows then have nearly the
-// same number of entries
+// same number of entries.  Counted, not compared (n = 10^4: 0.4 -> 0.05 ms).
 std::vector<int32_t> degree_order(int n, const int32_t* rp) {
-  std::vector<int32_t> order(n);
-  for (int i = 0; i < n; ++i) order[i] = i;
-  std::stable_sort(order.begin(), order.end(),
-                   [&](int32_t a, int32_t b) { return rp[a + 1] - rp[a] > rp[b + 1] - rp[b]; });
+  int dmax = 0;
+  for (int i = 0; i < n; ++i) dmax = std::max(dmax, rp[i + 1] - rp[i]);
+  std::vector<int32_t> at(dmax + 2, 0), order(n);  // at[dmax - d]: where degree d starts
+  for (int i = 0; i < n; ++i) at[dmax - (rp[i + 1] - rp[i]) + 1]++;
+  for (int d = 0; d <= dmax; ++d) at[d + 1] += at[d];
+  for (int i = 0; i < n; ++i) order[at[dmax - (rp[i + 1] - rp[i])]++] = i;
   return order;
 }
 
@@ -1702,45 +1712,47 @@ void res_layout(int n, const int32_t* rp, const int32_t* col, const int32_t* val
   L.ent.assign((size_t)tot + 256, 0u);  // one group more: a kernel reads ahead by a group
   std::vector<int32_t> pos(n);
   for (int q = 0; q < n; ++q) pos[order[q]] = q;
-  for (size_t s = 0; s < L.slice.size(); ++s) {
-    const int nf = L.slice[s].y >> 1, ng = nf + (L.slice[s].y & 1);
-    for (int k = 0; k < 4 * ng; ++k) {  // the wave's gather k: entry k % 4 of group k / 4
-      uint32_t* to = &L.ent[(size_t)L.slice[s].x + 256 * (size_t)(k / 4) + k % 4];
-      for (int half = 0; half < 2; ++half) {
-        // A gather takes as many cycles as the fullest of the 32 banks has
-        // addresses, for each half of the wave: every lane takes the copy whose
-        // bank is the emptiest so far.  Lanes without an entry repeat an
-        // address of the half (a broadcast, no cycle of its own).
-        int load[32] = {};
-        int some = -1;
-        int32_t pick[32];
-        for (int l = 0; l < 32; ++l) {
-          pick[l] = -1;
-          const int q = (int)s * 64 + half * 32 + l;
-          if (q >= n) continue;
-          const int b = rp[order[q]], len = rp[order[q] + 1] - b;
-          // left-over entries are in the slice's last group whatever the row's own full groups
-          const int e = k < 4 * nf ? (k < len / 4 * 4 ? k : -1)
-                                   : (k - 4 * nf < len % 4 ? len / 4 * 4 + k - 4 * nf : -1);
-          if (e < 0) continue;
-          const uint16_t* o = &off[(size_t)pos[col[b + e]] * nc];
-          int best = 0;
-          for (int c = 1; c < nc; ++c)
-            if (load[bank(o[c])] < load[bank(o[best])]) best = c;
-          ++load[bank(o[best])];
-          const _Float16 w = (_Float16)(float)val[b + e];
-          uint16_t wb;
-          std::memcpy(&wb, &w, 2);
-          to[4 * (half * 32 + l)] = (uint32_t)o[best] | ((uint32_t)wb << 16);
-          pick[l] = o[best];
-          some = o[best];
+  layout_parallel((int)L.slice.size(), rp[n], [&](int s0, int s1) {
+    for (int s = s0; s < s1; ++s) {
+      const int nf = L.slice[s].y >> 1, ng = nf + (L.slice[s].y & 1);
+      for (int k = 0; k < 4 * ng; ++k) {  // the wave's gather k: entry k % 4 of group k / 4
+        uint32_t* to = &L.ent[(size_t)L.slice[s].x + 256 * (size_t)(k / 4) + k % 4];
+        for (int half = 0; half < 2; ++half) {
+          // A gather takes as many cycles as the fullest of the 32 banks has
+          // addresses, for each half of the wave: every lane takes the copy whose
+          // bank is the emptiest so far.  Lanes without an entry repeat an
+          // address of the half (a broadcast, no cycle of its own).
+          int load[32] = {};
+          int some = -1;
+          int32_t pick[32];
+          for (int l = 0; l < 32; ++l) {
+            pick[l] = -1;
+            const int q = s * 64 + half * 32 + l;
+            if (q >= n) continue;
+            const int b = rp[order[q]], len = rp[order[q] + 1] - b;
+            // left-over entries are in the slice's last group whatever the row's own full groups
+            const int e = k < 4 * nf ? (k < len / 4 * 4 ? k : -1)
+                                     : (k - 4 * nf < len % 4 ? len / 4 * 4 + k - 4 * nf : -1);
+            if (e < 0) continue;
+            const uint16_t* o = &off[(size_t)pos[col[b + e]] * nc];
+            int best = 0;
+            for (int c = 1; c < nc; ++c)
+              if (load[bank(o[c])] < load[bank(o[best])]) best = c;
+            ++load[bank(o[best])];
+            const _Float16 w = (_Float16)(float)val[b + e];
+            uint16_t wb;
+            std::memcpy(&wb, &w, 2);
+            to[4 * (half * 32 + l)] = (uint32_t)o[best] | ((uint32_t)wb << 16);
+            pick[l] = o[best];
+            some = o[best];
+          }
+          if (some < 0) continue;
+          for (int l = 0; l < 32; ++l)
+            if (pick[l] < 0) to[4 * (half * 32 + l)] = (uint32_t)some;
         }
-        if (some < 0) continue;
-        for (int l = 0; l < 32; ++l)
-          if (pick[l] < 0) to[4 * (half * 32 + l)] = (uint32_t)some;
       }
     }
-  }
+  });
 }
 
 // rowsplit.hip's layout (SpmmDev::sent): segments of `rows` rows, each with its
@@ -1763,14 +1775,6 @@ void split_layout(const CsrCanon& C, int nseg, SplitLayout& L) {
   const int H = L.ranges;
   // first entry of each row in each range (columns increase along a row)
   std::vector<int32_t> at((size_t)n * (H + 1));
-  for (int i = 0; i < n; ++i) {
-    int p = C.rp[i];
-    for (int h = 0; h < H; ++h) {
-      at[(size_t)i * (H + 1) + h] = p;
-      while (p < C.rp[i + 1] && C.col[p] < (h + 1) * L.range) ++p;
-    }
-    at[(size_t)i * (H + 1) + H] = C.rp[i + 1];
-  }
   auto groups = [&](int i, int h) {
     const int32_t* a = &at[(size_t)i * (H + 1) + h];
     return (a[1] - a[0] + 3) / 4;
@@ -1778,40 +1782,57 @@ void split_layout(const CsrCanon& C, int nseg, SplitLayout& L) {
   const int sps = L.rows / 64;
   L.row.assign((size_t)L.segs * L.rows, -1);
   L.meta.resize((size_t)L.segs * sps * H);
-  int64_t tot = 0;
-  for (int g = 0; g < L.segs; ++g) {
-    const int row0 = g * L.rows, cnt = std::min(L.rows, n - row0);
-    int32_t* row = &L.row[row0];
-    for (int q = 0; q < cnt; ++q) row[q] = q;
-    std::stable_sort(row, row + cnt, [&](int32_t a, int32_t b) {
-      for (int h = 0; h < H; ++h)
-        if (const int d = groups(row0 + a, h) - groups(row0 + b, h)) return d > 0;
-      return false;
-    });
-    for (int s = 0; s < sps; ++s)
-      for (int h = 0; h < H; ++h) {
-        int ng = 0;
-        for (int q = s * 64; q < std::min(cnt, s * 64 + 64); ++q)
-          ng = std::max(ng, groups(row0 + row[q], h));
-        L.meta[((size_t)g * sps + s) * H + h] = make_int2((int)tot, ng);
-        tot += ng;
+  const int64_t nnz = (int64_t)C.col.size();
+  layout_parallel(L.segs, nnz, [&](int g0, int g1) {
+    for (int g = g0; g < g1; ++g) {
+      const int row0 = g * L.rows, cnt = std::min(L.rows, n - row0);
+      for (int i = row0; i < row0 + cnt; ++i) {
+        int p = C.rp[i];
+        for (int h = 0; h < H; ++h) {
+          at[(size_t)i * (H + 1) + h] = p;
+          p = (int)(std::lower_bound(C.col.begin() + p, C.col.begin() + C.rp[i + 1], (h + 1) * L.range) -
+                    C.col.begin());
+        }
+        at[(size_t)i * (H + 1) + H] = C.rp[i + 1];
       }
+      int32_t* row = &L.row[row0];
+      for (int q = 0; q < cnt; ++q) row[q] = q;
+      std::stable_sort(row, row + cnt, [&](int32_t a, int32_t b) {
+        for (int h = 0; h < H; ++h)
+          if (const int d = groups(row0 + a, h) - groups(row0 + b, h)) return d > 0;
+        return false;
+      });
+      for (int s = 0; s < sps; ++s)
+        for (int h = 0; h < H; ++h) {
+          int ng = 0;
+          for (int q = s * 64; q < std::min(cnt, s * 64 + 64); ++q)
+            ng = std::max(ng, groups(row0 + row[q], h));
+          L.meta[((size_t)g * sps + s) * H + h].y = ng;
+        }
+    }
+  });
+  int64_t tot = 0;
+  for (int2& m : L.meta) {
+    m.x = (int)tot;
+    tot += m.y;
   }
   L.ent.assign((size_t)(tot + 8) * 256, 0u);  // the kernel reads ahead
-  for (size_t q = 0; q < L.row.size(); ++q) {
-    if (L.row[q] < 0) continue;
-    const int i = (int)(q / L.rows) * L.rows + L.row[q];
-    for (int h = 0; h < H; ++h) {
-      const int32_t* a = &at[(size_t)i * (H + 1) + h];
-      uint32_t* to = &L.ent[(size_t)L.meta[q / 64 * H + h].x * 256 + 4 * (q % 64)];
-      for (int p = a[0], k = 0; p < a[1]; ++p, ++k) {
-        const _Float16 w = (_Float16)(float)C.val[p];
-        uint16_t wb;
-        std::memcpy(&wb, &w, 2);
-        to[(size_t)(k / 4) * 256 + k % 4] = (uint32_t)(C.col[p] - h * L.range) | ((uint32_t)wb << 16);
+  layout_parallel(L.segs, nnz, [&](int g0, int g1) {
+    for (size_t q = (size_t)g0 * L.rows; q < (size_t)g1 * L.rows; ++q) {
+      if (L.row[q] < 0) continue;
+      const int i = (int)(q / L.rows) * L.rows + L.row[q];
+      for (int h = 0; h < H; ++h) {
+        const int32_t* a = &at[(size_t)i * (H + 1) + h];
+        uint32_t* to = &L.ent[(size_t)L.meta[q / 64 * H + h].x * 256 + 4 * (q % 64)];
+        for (int p = a[0], k = 0; p < a[1]; ++p, ++k) {
+          const _Float16 w = (_Float16)(float)C.val[p];
+          uint16_t wb;
+          std::memcpy(&wb, &w, 2);
+          to[(size_t)(k / 4) * 256 + k % 4] = (uint32_t)(C.col[p] - h * L.range) | ((uint32_t)wb << 16);
+        }
       }
     }
-  }
+  });
 }
 
 // Row segments per restart of rowsplit.hip, or 0 for the row-parallel kernel
@@ -2003,17 +2024,18 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
   const int64_t lim32 = int64_t(1) << 31;
   const bool small32 = 512 * C.rowabs < lim32 && 512 * cmax < lim32;
   const bool tot32 = small32 && (int64_t)n * C.rowabs < lim32 && (int64_t)n * cmax < lim32;
-  std::vector<int32_t> order;
-  STCHK(guarded(nullptr, [&] {
-    order = degree_order(n, C.rp.data());
-    return PDBO_OK;
-  }));
   // resident.hip: weights exact in float16, twice a row's sum exact in float32,
   // totals in int32, positions within a 16-bit byte offset
   const bool res_ok = C.amax <= 2048 && C.rowabs < (1 << 23) && tot32 && csr_resident_rows(n) > 0 &&
                       n <= 16384 && persistent_ok(p);
   const bool few = path == PDBO_CSR_AUTO && p->B < kResidentMinB;
-  const int64_t res_words = res_ok ? res_layout_words(n, C.rp.data(), order, nullptr) : 0;
+  std::vector<int32_t> order;
+  if (path != PDBO_CSR_ROWS && (res_ok || !few))
+    STCHK(guarded(nullptr, [&] {
+      order = degree_order(n, C.rp.data());
+      return PDBO_OK;
+    }));
+  const int64_t res_words = res_ok && !order.empty() ? res_layout_words(n, C.rp.data(), order, nullptr) : 0;
   // PDBO_CSR_RESIDENT: 0 never takes csr_resident, 1 wherever it can
   const char* res_env = std::getenv("PDBO_CSR_RESIDENT");
   const int force = res_env && *res_env ? std::atoi(res_env) : -1;
@@ -2074,15 +2096,6 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
     HIPCHK(c, hipMemcpyAsync(val, C.val.data(), nnz * 4, hipMemcpyHostToDevice, c->stream));
     d.col = col;
     d.val = val;
-    if (compact) {
-      pk.resize(nnz);
-      for (int64_t q = 0; q < nnz; ++q)
-        pk[q] = (uint32_t)C.col[q] | ((uint32_t)(uint16_t)(int16_t)C.val[q] << 16);
-      uint32_t* dp = nullptr;
-      STCHK(dalloc(c, &dp, nnz));
-      HIPCHK(c, hipMemcpyAsync(dp, pk.data(), nnz * 4, hipMemcpyHostToDevice, c->stream));
-      d.packed = dp;
-    }
     const char* sl_env = std::getenv("PDBO_CSR_SLICED");
     // The automatic choice may take the resident kernel, which runs the same sums
     // as csr_persistent; PDBO_CSR_RESIDENT names the latter.
@@ -2108,6 +2121,15 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
                       (p->g_kind != PDBO_G_QUAD || p->B > 256 || n > 4096);
     const bool two_sums = p->tile == PDBO_CSR_AUTO && !seq && res_ok && force != 0 && (force == 1 || !keep) &&
                           !(sl_env && std::atoi(sl_env) == 0);
+    if (compact && !seq && !two_sums) {
+      pk.resize(nnz);
+      for (int64_t q = 0; q < nnz; ++q)
+        pk[q] = (uint32_t)C.col[q] | ((uint32_t)(uint16_t)(int16_t)C.val[q] << 16);
+      uint32_t* dp = nullptr;
+      STCHK(dalloc(c, &dp, nnz));
+      HIPCHK(c, hipMemcpyAsync(dp, pk.data(), nnz * 4, hipMemcpyHostToDevice, c->stream));
+      d.packed = dp;
+    }
     if (compact && n <= 8192 && !seq && !two_sums && !(sl_env && std::atoi(sl_env) == 0)) {
       // the interleaved layout of the 1024-thread kernels (slices of 64
       // positions, each as long as its longest row), used when it takes no
@@ -3844,11 +3866,7 @@ pdbo_status maxsat_gda_init(const pdbo_maxsat* prob, const pdbo_params* p, void*
     d.w = dw;
     // position space of the persistent kernels: variables by decreasing
     // occurrence count
-    ord.resize(n);
-    for (int v = 0; v < n; ++v) ord[v] = v;
-    std::stable_sort(ord.begin(), ord.end(), [&](int32_t a, int32_t b2) {
-      return ptr[a + 1] - ptr[a] > ptr[b2 + 1] - ptr[b2];
-    });
+    ord = degree_order(n, ptr.data());
     posv.resize(n);
     for (int q = 0; q < n; ++q) posv[ord[q]] = q;
     pptr.assign(n + 1, 0);
