@@ -1739,7 +1739,8 @@ void res_layout(int n, const int32_t* rp, const int32_t* col, const int32_t* val
             for (int c = 1; c < nc; ++c)
               if (load[bank(o[c])] < load[bank(o[best])]) best = c;
             ++load[bank(o[best])];
-            const _Float16 w = (_Float16)(float)val[b + e];
+            // (bits of zero mark padding: an entry of weight zero has -0)
+            const _Float16 w = (_Float16)(val[b + e] ? (float)val[b + e] : -0.f);
             uint16_t wb;
             std::memcpy(&wb, &w, 2);
             to[4 * (half * 32 + l)] = (uint32_t)o[best] | ((uint32_t)wb << 16);

@@ -258,6 +258,25 @@ __global__ void __launch_bounds__(kKrThreads) kcut_resident(KcutDev D, int nstep
           for (int u = 0; u < K; ++u) acc[u] = fmaf(weight(e[m]), v[m][u], acc[u]);
       }
       if (ng == 0) cur = load(nx, 0);
+      // X is at most 1 or, where a node's logits have overflowed, NaN in all its
+      // words.  Padding entries gather other rows' words: a wave that meets a NaN
+      // sums again without them.
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(acc[0] != acc[0]) != 0, 0)) {
+#pragma unroll
+        for (int u = 0; u < K; ++u) acc[u] = 0.f;
+#pragma unroll 1
+        for (int g = 0; g < ng; ++g) {
+          const ku32x4 e = load(sl, g);
+#pragma unroll 1
+          for (int m = 0; m < 4; ++m) {
+            float v[K];
+            kr_read<K>(e[m] & 0xffffu, v);
+#pragma unroll
+            for (int u = 0; u < K; ++u)
+              acc[u] = e[m] >> 16 ? fmaf(weight(e[m]), v[u], acc[u]) : acc[u];
+          }
+        }
+      }
       sl = nx;
       const float y = yr[j];
       float gr[K], m = 0.f;

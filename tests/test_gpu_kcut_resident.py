@@ -95,3 +95,47 @@ def test_times_of_improvements(B, monkeypatch):
         out.append((tr["t"], tr["F"], tr["b"], r["best_obj"], r["best_x"]))
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("n,m,k", [(300, 450, 2), (2000, 3000, 3), (3000, 8000, 4), (1500, 2000, 7)])
+def test_nan_stays_with_its_neighbours(n, m, k, monkeypatch):
+    """A dual so large that the logits of its node overflow: NaN reaches the node's
+    neighbours, an edge at an iteration, and no other node; an edge of weight zero
+    carries it too."""
+    P = require_gpu()
+    g = W.kcut_graph(n, m, k, rep=8)
+    hub = int(np.diff(g.row_ptr).argmax())
+    far = int(g.col_idx[g.row_ptr[hub]])
+    for i, j in ((hub, far), (far, hub)):
+        g.w[g.row_ptr[i] + int(np.searchsorted(g.col_idx[g.row_ptr[i]:g.row_ptr[i + 1]], j))] = 0
+    B = 4
+    Y = np.full((B, n), 0.5, np.float32)
+    Y[1, hub] = Y[2, n // 2] = 3e38
+    for kind in ("quad", "entropy"):
+        out = []
+        for res in ("1", "0"):
+            say(f"[kcut nan] n={n} k={k} g={kind} resident={res}")
+            monkeypatch.setenv("PDBO_KCUT_RESIDENT", res)
+            ctx = P.kcut_gda_init(g, _params(B, kind, 0.01), None)
+            ctx.set_state(None, Y, 0)
+            got = []
+            for t in (1, 1, 2):
+                ctx.step(t)
+                got += [*ctx.get_state()[:2], ctx.objectives()]
+            r, tr = ctx.result(), ctx.trace()
+            got += [r["best_obj"], r["best_x"], tr["t"], tr["F"], tr["b"]]
+            ctx.destroy()
+            out.append(got)
+        for a, b in zip(*out):
+            a, b = np.asarray(a), np.asarray(b)
+            assert np.array_equal(a, b, equal_nan=a.dtype == np.float32)
+        if kind == "quad":
+            # 2 x y overflows at the first or, x being a unit vector by then, the
+            # second iteration; after four NaN is one to three edges away
+            bad = np.isnan(out[1][6].reshape(B, n, k)).any(axis=2)
+            near = np.zeros(n, bool)
+            near[hub] = True
+            row = np.repeat(np.arange(n), np.diff(g.row_ptr))
+            for _ in range(3):
+                near[g.col_idx[near[row]]] = True
+            assert not bad[0].any() and bad[1, hub] and bad[1, far] and (bad[1] <= near).all()
