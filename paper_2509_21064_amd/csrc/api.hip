@@ -226,6 +226,23 @@ pdbo_status dalloc(pdbo_ctx* c, T** p, size_t count) {
   return PDBO_OK;
 }
 
+// f() prepares what a faster path needs and the context can do without: where
+// memory runs out in it, what it allocated is freed and `have` is false.
+template <typename F>
+pdbo_status optional_part(pdbo_ctx* c, bool& have, F f) {
+  const size_t mark = c->allocs.size();
+  const std::string err0 = g_last_error;
+  const pdbo_status st = guarded(c, f);
+  have = st == PDBO_OK;
+  if (st != PDBO_ENOMEM) return st;
+  (void)hipStreamSynchronize(c->stream);
+  for (size_t k = mark; k < c->allocs.size(); ++k) (void)hipFree(c->allocs[k]);
+  c->allocs.resize(mark);
+  c->err.clear();
+  g_last_error = err0;
+  return PDBO_OK;
+}
+
 void free_all(pdbo_ctx* c) {
   if (!c) return;
   // the context's stream may be the null (legacy default) stream: synchronise it either way
@@ -1064,20 +1081,6 @@ pdbo_status setup_frags(pdbo_ctx* c) {
   HIPCHK(c, hipMemcpyAsync(c->frag_tiles_d, c->frag_tiles_h.data(),
                            c->frag_tiles_h.size() * sizeof(TileDev), hipMemcpyHostToDevice, c->stream));
   return frag_shadow(c);
-}
-
-// Back to the workgroup tiles; `mark`: the context's allocations before setup_frags.
-void drop_frags(pdbo_ctx* c, size_t mark) {
-  (void)hipStreamSynchronize(c->stream);
-  for (size_t k = mark; k < c->allocs.size(); ++k) (void)hipFree(c->allocs[k]);
-  c->allocs.resize(mark);
-  for (InstDev& I : c->insts_h) {
-    I.Af = nullptr;
-    I.Xf[0] = I.Xf[1] = nullptr;
-  }
-  c->frag_tiles_d = nullptr;
-  c->frag = -1;
-  c->err.clear();
 }
 
 pdbo_status upload_dense_tables(pdbo_ctx* c) {
@@ -1972,11 +1975,15 @@ static pdbo_status dense_init(int k, const pdbo_qubo* probs, const pdbo_params* 
     const char* e = std::getenv("PDBO_FRAG");
     c->frag = e && *e ? std::min(std::atoi(e), dense_num_frags()) - 1 : frag_choice(c);
     if (c->frag >= 0) {
-      const size_t mark = c->allocs.size();
-      st = guarded(c, [&] { return setup_frags(c); });
-      if (st == PDBO_ENOMEM) {  // no room for the copies: the tiles, same bits
-        drop_frags(c, mark);
-        st = PDBO_OK;
+      bool have = false;
+      st = optional_part(c, have, [&] { return setup_frags(c); });
+      if (!have) {  // no room for the copies: the tiles, same bits
+        for (InstDev& I : c->insts_h) {
+          I.Af = nullptr;
+          I.Xf[0] = I.Xf[1] = nullptr;
+        }
+        c->frag_tiles_d = nullptr;
+        c->frag = -1;
       }
     }
   }
@@ -2058,6 +2065,8 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
   STCHK(persistent_supported(p));
   if (!fits)
     return fail(nullptr, PDBO_EUNSUPPORTED, "instance too large for the restart-resident CSR kernel");
+  const std::string err0 = g_last_error;
+  bool no_room = false;
   pdbo_ctx* c = new pdbo_ctx();
   c->kind = 1;
   c->compact = compact;
@@ -2120,8 +2129,39 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
     // entropy: 13 / 24).
     const bool keep = n <= 8192 && csr_entries_in_lds(n, nnz, compact) &&
                       (p->g_kind != PDBO_G_QUAD || p->B > 256 || n > 4096);
-    const bool two_sums = p->tile == PDBO_CSR_AUTO && !seq && res_ok && force != 0 && (force == 1 || !keep) &&
-                          !(sl_env && std::atoi(sl_env) == 0);
+    bool two_sums = p->tile == PDBO_CSR_AUTO && !seq && res_ok && force != 0 && (force == 1 || !keep) &&
+                    !(sl_env && std::atoi(sl_env) == 0);
+    if (seq || two_sums) {
+      bool have = false;
+      STCHK(optional_part(c, have, [&]() -> pdbo_status {
+        csr_res_layout(C, order, rl);
+        uint32_t* re = nullptr;
+        int2* rs = nullptr;
+        int32_t* rc = nullptr;
+        STCHK(dalloc(c, &re, rl.ent.size()));
+        STCHK(dalloc(c, &rs, rl.slice.size()));
+        STCHK(dalloc(c, &rc, rl.cp.size()));
+        if (seq) {
+          STCHK(dalloc(c, &d.rtr, (size_t)B * kResTrace));
+          STCHK(dalloc(c, &d.rtl, B));
+        }
+        HIPCHK(c, hipMemcpyAsync(re, rl.ent.data(), rl.ent.size() * 4, hipMemcpyHostToDevice, c->stream));
+        HIPCHK(c, hipMemcpyAsync(rs, rl.slice.data(), rl.slice.size() * sizeof(int2), hipMemcpyHostToDevice,
+                                 c->stream));
+        HIPCHK(c, hipMemcpyAsync(rc, rl.cp.data(), rl.cp.size() * 4, hipMemcpyHostToDevice, c->stream));
+        d.rent = re;
+        d.nrent = res_words;
+        d.rslice = rs;
+        d.rcp = rc;
+        return PDBO_OK;
+      }));
+      if (!have) {  // csr_persistent, or (few restarts) the row-parallel path: same bits
+        rl = ResLayout();
+        no_room = seq;
+        if (no_room) return PDBO_ENOMEM;
+        two_sums = false;
+      }
+    }
     if (compact && !seq && !two_sums) {
       pk.resize(nnz);
       for (int64_t q = 0; q < nnz; ++q)
@@ -2164,23 +2204,6 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
         d.nsl = tot;
       }
     }
-    if (seq || two_sums) {
-      csr_res_layout(C, order, rl);
-      uint32_t* re = nullptr;
-      int2* rs = nullptr;
-      int32_t* rc = nullptr;
-      STCHK(dalloc(c, &re, rl.ent.size()));
-      STCHK(dalloc(c, &rs, rl.slice.size()));
-      STCHK(dalloc(c, &rc, rl.cp.size()));
-      HIPCHK(c, hipMemcpyAsync(re, rl.ent.data(), rl.ent.size() * 4, hipMemcpyHostToDevice, c->stream));
-      HIPCHK(c, hipMemcpyAsync(rs, rl.slice.data(), rl.slice.size() * sizeof(int2), hipMemcpyHostToDevice,
-                               c->stream));
-      HIPCHK(c, hipMemcpyAsync(rc, rl.cp.data(), rl.cp.size() * 4, hipMemcpyHostToDevice, c->stream));
-      d.rent = re;
-      d.nrent = res_words;
-      d.rslice = rs;
-      d.rcp = rc;
-    }
     std::vector<float> hcps(ld, 0.f);
     std::vector<int64_t> hcp(ld, 0);
     for (int i = 0; i < n; ++i) {
@@ -2207,8 +2230,6 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
     if (seq) {
       d.seq = 1;
       d.trace_cap = kTraceCap;
-      STCHK(dalloc(c, &d.rtr, (size_t)B * kResTrace));
-      STCHK(dalloc(c, &d.rtl, B));
       STCHK(dalloc(c, &d.trace, kTraceCap));
       STCHK(dalloc(c, &d.trace_len, 1));
       STCHK(dalloc(c, &d.t_dev, 1));
@@ -2227,6 +2248,11 @@ static pdbo_status csr_init(const pdbo_qubo* q, const pdbo_params* p, void* stre
     return PDBO_OK;
   };
   if (st == PDBO_OK) st = guarded(c, run);
+  if (no_room) {
+    pdbo_destroy(c);
+    g_last_error = err0;
+    return spmm_init(&C, nullptr, p, stream, out);
+  }
   if (st != PDBO_OK) {
     const std::string msg = c->err.empty() ? g_last_error : c->err;
     pdbo_destroy(c);
@@ -2273,24 +2299,32 @@ static pdbo_status spmm_init(const CsrCanon* C, const RealCanon* R, const pdbo_p
     SplitLayout split;  // host staging, alive until init syncs
     // the segments' layout and restart-major state, or node-major row-parallel
     if (const int nseg = C ? split_choice(*C, B) : 0) {
-      split_layout(*C, nseg, split);
-      d.grid = split.segs;
-      uint32_t* ent = nullptr;
-      int2* meta = nullptr;
-      int32_t* row = nullptr;
-      STCHK(dalloc(c, &ent, split.ent.size()));
-      STCHK(dalloc(c, &meta, split.meta.size()));
-      STCHK(dalloc(c, &row, split.row.size()));
-      HIPCHK(c, hipMemcpyAsync(ent, split.ent.data(), split.ent.size() * 4, hipMemcpyHostToDevice, c->stream));
-      HIPCHK(c, hipMemcpyAsync(meta, split.meta.data(), split.meta.size() * sizeof(int2),
-                               hipMemcpyHostToDevice, c->stream));
-      HIPCHK(c, hipMemcpyAsync(row, split.row.data(), split.row.size() * 4, hipMemcpyHostToDevice, c->stream));
-      d.sent = ent;
-      d.smeta = meta;
-      d.srow = row;
-      d.srows = split.rows;
-      d.srange = split.range;
-      d.sranges = split.ranges;
+      bool have = false;
+      STCHK(optional_part(c, have, [&]() -> pdbo_status {
+        split_layout(*C, nseg, split);
+        uint32_t* ent = nullptr;
+        int2* meta = nullptr;
+        int32_t* row = nullptr;
+        STCHK(dalloc(c, &ent, split.ent.size()));
+        STCHK(dalloc(c, &meta, split.meta.size()));
+        STCHK(dalloc(c, &row, split.row.size()));
+        HIPCHK(c, hipMemcpyAsync(ent, split.ent.data(), split.ent.size() * 4, hipMemcpyHostToDevice, c->stream));
+        HIPCHK(c, hipMemcpyAsync(meta, split.meta.data(), split.meta.size() * sizeof(int2),
+                                 hipMemcpyHostToDevice, c->stream));
+        HIPCHK(c, hipMemcpyAsync(row, split.row.data(), split.row.size() * 4, hipMemcpyHostToDevice, c->stream));
+        d.sent = ent;
+        d.smeta = meta;
+        d.srow = row;
+        return PDBO_OK;
+      }));
+      if (have) {
+        d.grid = split.segs;
+        d.srows = split.rows;
+        d.srange = split.range;
+        d.sranges = split.ranges;
+      } else {  // the row-parallel kernel, same bits
+        split = SplitLayout();
+      }
     }
     int32_t *rp = nullptr, *col = nullptr;
     float* cps = nullptr;
@@ -3590,32 +3624,40 @@ pdbo_status kcut_gda_init(const pdbo_kcut* g, const pdbo_params* p, void* stream
       res = (res_env && std::atoi(res_env) == 1) || kcut_resident_us(n, k, B, res_layout_words(n, g->row_ptr, order, nullptr)) <
             kcut_rows_us(n, k, B, nnz);
     }
-    if (res) {
-      std::vector<uint16_t> off((size_t)nc * n);
-      for (int q = 0; q < n; ++q)
-        for (int cc = 0; cc < nc; ++cc) off[(size_t)q * nc + cc] = (uint16_t)kcutres_word(n, k, cc, q);
-      res_layout(n, g->row_ptr, g->col_idx, g->w, order, nc, off, [](uint16_t o) { return o % 32; }, rl);
-      uint32_t* re = nullptr;
-      int2* rs = nullptr;
-      int32_t* ro = nullptr;
-      STCHK(dalloc(c, &re, rl.ent.size()));
-      STCHK(dalloc(c, &rs, rl.slice.size()));
-      STCHK(dalloc(c, &ro, n));
-      HIPCHK(c, hipMemcpyAsync(re, rl.ent.data(), rl.ent.size() * 4, hipMemcpyHostToDevice, c->stream));
-      HIPCHK(c, hipMemcpyAsync(rs, rl.slice.data(), rl.slice.size() * sizeof(int2), hipMemcpyHostToDevice,
-                               c->stream));
-      HIPCHK(c, hipMemcpyAsync(ro, order.data(), (size_t)n * 4, hipMemcpyHostToDevice, c->stream));
-      d.rent = re;
-      d.rslice = rs;
-      d.order = ro;
-      STCHK(dalloc(c, &d.rbestF, B));
-      STCHK(dalloc(c, &d.rbestT, B));
-      STCHK(dalloc(c, &d.best_xr, (size_t)B * n));
-      STCHK(dalloc(c, &d.rtr, (size_t)B * kResTrace));
-      STCHK(dalloc(c, &d.rtl, B));
-      HIPCHK(c, launch_fill_i64(d.rbestF, kI64Max, B, c->stream));
-      HIPCHK(c, launch_fill_i64(d.rbestT, kI64Max, B, c->stream));
-    } else {
+    if (res)
+      STCHK(optional_part(c, res, [&]() -> pdbo_status {
+        std::vector<uint16_t> off((size_t)nc * n);
+        for (int q = 0; q < n; ++q)
+          for (int cc = 0; cc < nc; ++cc) off[(size_t)q * nc + cc] = (uint16_t)kcutres_word(n, k, cc, q);
+        res_layout(n, g->row_ptr, g->col_idx, g->w, order, nc, off, [](uint16_t o) { return o % 32; }, rl);
+        uint32_t* re = nullptr;
+        int2* rs = nullptr;
+        int32_t* ro = nullptr;
+        STCHK(dalloc(c, &re, rl.ent.size()));
+        STCHK(dalloc(c, &rs, rl.slice.size()));
+        STCHK(dalloc(c, &ro, n));
+        STCHK(dalloc(c, &d.rbestF, B));
+        STCHK(dalloc(c, &d.rbestT, B));
+        STCHK(dalloc(c, &d.best_xr, (size_t)B * n));
+        STCHK(dalloc(c, &d.rtr, (size_t)B * kResTrace));
+        STCHK(dalloc(c, &d.rtl, B));
+        HIPCHK(c, hipMemcpyAsync(re, rl.ent.data(), rl.ent.size() * 4, hipMemcpyHostToDevice, c->stream));
+        HIPCHK(c, hipMemcpyAsync(rs, rl.slice.data(), rl.slice.size() * sizeof(int2), hipMemcpyHostToDevice,
+                                 c->stream));
+        HIPCHK(c, hipMemcpyAsync(ro, order.data(), (size_t)n * 4, hipMemcpyHostToDevice, c->stream));
+        HIPCHK(c, launch_fill_i64(d.rbestF, kI64Max, B, c->stream));
+        HIPCHK(c, launch_fill_i64(d.rbestT, kI64Max, B, c->stream));
+        d.rent = re;
+        d.rslice = rs;
+        d.order = ro;
+        return PDBO_OK;
+      }));
+    if (!res) {  // the row-parallel kernels, same bits where there was no room
+      rl = ResLayout();
+      d.rbestF = d.rbestT = nullptr;
+      d.best_xr = nullptr;
+      d.rtr = nullptr;
+      d.rtl = nullptr;
       STCHK(dalloc(c, &d.X[0], sz));
       STCHK(dalloc(c, &d.X[1], sz));
       STCHK(dalloc(c, &d.part, (size_t)d.grid * d.W));

@@ -85,3 +85,57 @@ def test_host_allocation_failure_frees_the_device(kind, monkeypatch):
         assert torch.cuda.mem_get_info()[0] >= free0 - (2 << 20), k
     assert failures >= 4
     mk().destroy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["csr", "csr_many", "split", "kcut"])
+@pytest.mark.parametrize("host", [False, True])
+def test_no_room_for_the_layout(kind, host, monkeypatch):
+    """The layouts of csr_resident, csr_split and kcut_resident are optional: an
+    allocation of theirs that fails, on the device or the host, leaves the context
+    on the kernels it would otherwise run on, with the same run."""
+    import numpy as np
+    from gpu_util import require_gpu, say
+    P = require_gpu()
+    if kind == "kcut":
+        g = W.kcut_graph(400, 1200, 3, rep=1)
+        mk = lambda: P.kcut_gda_init(g, dict(B=8, T=1, alpha=0.01, beta=0.01, y0=0.5, delta=2.0 ** -7, scale=1.0,
+                                             g="quad", seed=3), None)
+    else:
+        if kind == "split":
+            monkeypatch.setenv("PDBO_CSR_SPLIT", "1")
+        q = W.maxcut_c2(0, n=400, M=1200)
+        p = W.gda_params("maxcut", B=130 if kind == "csr_many" else 8, T=1, tile=2 if kind == "split" else 0, seed=5)
+        mk = lambda: P.qubo_gda_init(q, p, None)
+    # allocations of the layout, and what the context runs on with and without it
+    parts, names = {"csr": (5, ("csr_resident_seq", "csr_rows")), "csr_many": (3, ("csr_resident", "csr_packed_dbuf_t32")),
+                    "split": (3, ("csr_split", "csr_rows")), "kcut": (8, ("", ""))}[kind]
+
+    def run():
+        ctx = mk()
+        name = ctx.tile_name
+        ctx.step(30)
+        r = ctx.result()
+        out = [*ctx.get_state()[:2], ctx.objectives(), r["best_obj"], r["best_x"]]
+        ctx.destroy()
+        return name, out
+
+    name, ref = run()
+    assert name == names[0]
+    if host:
+        monkeypatch.setenv("PDBO_FAIL_ALLOC_HOST", "1")
+    refused, fell_back = [], 0
+    for k in range(1, 40):
+        say(f"[no room] {kind} allocation {k} host={host}")
+        monkeypatch.setenv("PDBO_FAIL_ALLOC_AT", str(k))
+        try:
+            name, got = run()
+            fell_back += name == names[1]
+            for a, b in zip(got, ref):
+                assert np.array_equal(a, b)
+        except P.PdboError as e:
+            assert e.status == 2
+            refused.append(k)
+        monkeypatch.setenv("PDBO_FAIL_ALLOC_AT", "0")
+    assert max(refused) - len(refused) == parts
+    assert kind == "kcut" or fell_back == parts
