@@ -19,7 +19,7 @@
 // exact below 2^24.
 //
 // Measured at that size: 21 us a launch (row-parallel 45), of which the gathers
-// take the LDS about 10; four groups of entries in flight (left to itself the
+// take the LDS about 12 (25,400 of 44,000 cycles); four groups of entries in flight (left to itself the
 // compiler loads a group and waits for it: 31 us; eight in flight: 23), the next
 // range's x loaded during the gathers, and the sums put back into row order
 // through LDS for the update (row by row in slice order it took 6 us more).
