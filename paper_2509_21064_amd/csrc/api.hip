@@ -3356,9 +3356,13 @@ pdbo_status qubo_dual_bound(pdbo_ctx* c, double ybar, int32_t iters, double* low
     }
     if (st == PDBO_OK) st = need(&c->cert_xf, 2 * 16 * (size_t)rb);
     if (st == PDBO_OK) st = need(&c->cert_tiles, (size_t)(n + 15) / 16);
+    std::vector<TileDev> tiles;
+    if (st == PDBO_OK)
+      st = guarded(c, [&] {
+        for (int m = 0; m < (n + 15) / 16; ++m) tiles.push_back(TileDev{0, 16 * m, 0, m});
+        return PDBO_OK;
+      });
     if (st == PDBO_OK) {
-      std::vector<TileDev> tiles;
-      for (int m = 0; m < (n + 15) / 16; ++m) tiles.push_back(TileDev{0, 16 * m, 0, m});
       HIPCHK(c, hipMemcpy(c->cert_tiles, tiles.data(), tiles.size() * sizeof(TileDev),
                           hipMemcpyHostToDevice));
       c->cert_frag = true;
