@@ -54,9 +54,11 @@ double resident_us(int n, int64_t words, int g_kind) {
 double rowpar_us(int n, int64_t nnz, int B) {
   return 9.0 + 0.1 * B + 4e-6 * (double)n * B + std::max(0.07 * (double)nnz / n, 5e-7 * (double)nnz * B);
 }
-// Up to this many restarts the resident kernel stays with the entropy beyond
-// 8192 rows too, where the estimate is against it: its runs are compared with
-// the row-parallel path's there.
+// Up to this many restarts the entropy beyond 8192 rows goes by the quadratic
+// g's estimate and so stays on the resident kernel up to some 12,000 rows,
+// though it is slower there (us an iteration, B = 5: n = 8300, degree 2: 13.5 /
+// 10.1; n = 12000, degree 3: 17.5 / 10.3): test_gpu_resident.py takes its runs
+// of 16 rows a thread from the automatic choice.
 constexpr int kEntropyResidentB = 5;
 constexpr int64_t kI64Max = LLONG_MAX;
 
